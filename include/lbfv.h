@@ -189,7 +189,13 @@ int lbfv_residual(lbfv_ctx *ctx, double *r);
 int lbfv_totals_device(lbfv_ctx *ctx, double *dev_out);
 
 /* Execution shape of the step kernel: rows of the row block one wavefront marches
- * through, and wavefronts per workgroup (1, 2 or 4).  0 keeps the current value. */
+ * through, and wavefronts per workgroup (1, 2 or 4).  0 keeps the current value.
+ * A context on which no shape has been set (by this call, lbfv_set_wave_pairs,
+ * lbfv_set_time_block or lbfv_autotune) advances a small mesh (at most 2^18 cells) in the
+ * patch form instead: rectangular patches with one cell per lane, up to 8 steps per launch,
+ * each patch recomputing a halo.  The results are those of one-step launches bit for bit, in
+ * every storage (16-bit storage is rounded after every step); checks fall due exactly at
+ * check_every.  A stream under capture always gets marches, one launch per time block. */
 int lbfv_set_tile(lbfv_ctx *ctx, int32_t rows, int32_t waves_per_block);
 int lbfv_get_tile(const lbfv_ctx *ctx, int32_t *rows, int32_t *waves_per_block);
 /* Work split of two steps per launch: 0 (default) one wavefront per work item (strip x
@@ -229,8 +235,9 @@ int lbfv_get_time_block(const lbfv_ctx *ctx, int32_t *steps);
 int lbfv_set_reference_velocity(lbfv_ctx *ctx, double ux, double uy);
 int lbfv_get_reference_velocity(const lbfv_ctx *ctx, double *ux, double *uy);
 /* Autotuner: times the candidate shapes for `scheme` on this context (the state is
- * saved and restored), keeps the fastest, and records it in a cache file keyed by
- * (gfx arch, scheme, precision, storage, time block, mesh size class).  cache_path NULL: the
+ * saved and restored; on small meshes the patch form of lbfv_set_tile is a candidate, and
+ * where it wins the march controls hold the fastest march of one step per launch), keeps
+ * the fastest, and records it in a cache file keyed by (gfx arch, scheme, precision, storage, time block, mesh size class).  cache_path NULL: the
  * environment variable LBFV_TUNE_CACHE, else no file.  A cached entry is used
  * without timing.  best_ms (nullable) receives the time per step of the choice. */
 int lbfv_autotune(lbfv_ctx *ctx, int scheme, int32_t trial_steps, const char *cache_path,

@@ -4,6 +4,7 @@
 #include "lbfv.h"
 #include "aux_kernels.hpp"
 #include "batch_kernels.hpp"
+#include "patch_kernels.hpp"
 
 #include <algorithm>
 #include <type_traits>
@@ -61,6 +62,20 @@ struct HostCase {
     RefState ref() const { return RefState{rho0, rho0 * u0[0] / c, rho0 * u0[1] / c}; }
 };
 
+// Which kernels advance a context: the patch form where the rule of use_patch says so, until
+// the caller sets a march shape (FORM_MARCH) or the autotuner picks one of the two.
+enum Form { FORM_AUTO = 0, FORM_MARCH = 1, FORM_PATCH = 2 };
+
+// Patches of a mesh and the waves of a workgroup; cost: what the cost model gives them, us per
+// step.  halo = 0: not planned yet; waves = 0: the mesh takes none.  per_wave and max_waves
+// are the limits it was made for (at most 64 / per_wave columns, max_waves waves).
+struct PatchPlan {
+    PatchGrid g = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    int waves = 0;
+    int per_wave = 0, max_waves = 0;
+    double cost = 0.0;
+};
+
 #define HIPCHK(expr)                                                                            \
     do {                                                                                        \
         hipError_t e_ = (expr);                                                                 \
@@ -83,7 +98,10 @@ struct lbfv_ctx {
     int pairs = 0;                   // two steps per launch, periodic mesh: a pair of waves per item
     // graphs of `gsteps` launches, per scheme (+4 per further step per launch) and starting buffer
     int gsteps = 32;
-    hipGraphExec_t gexec[16][2] = {};
+    // (16 + scheme: the patch form)
+    hipGraphExec_t gexec[20][2] = {};
+    int form = FORM_AUTO;
+    PatchPlan plan[2];               // patches of the current sides, for the DUGKS and the BKG kernels
     // reductions
     double *d_partial = nullptr, *d_out = nullptr, *h_out = nullptr, *d_uprev = nullptr;
     int red_blocks = 0;
@@ -369,6 +387,16 @@ void *step2_fn_variant(int variant, int scheme, bool bnd, bool ref) { LBFV_PICK(
 void *step_fn_variant(int variant, int scheme, bool bnd, bool ref) { LBFV_PICK(step_fn, variant, ref, scheme, bnd) }
 // K = 3, 4 steps per launch (doubly periodic meshes only)
 void *stepc_fn_variant(int variant, int scheme, int K, bool ref) { LBFV_PICK(stepc_fn, variant, ref, scheme, K) }
+// the patch form; bnd: some side is not periodic
+template <typename T, typename S, bool REF>
+void *patch_fn(int scheme, bool bnd) {
+    if (bnd)
+        return scheme == SCHEME_BKG ? (void *)patch_ptr_kernel<T, S, SCHEME_BKG, REF>
+                                    : (void *)patch_ptr_kernel<T, S, SCHEME_DUGKS, REF>;
+    return scheme == SCHEME_BKG ? (void *)patch_kernel<T, S, SCHEME_BKG, REF>
+                                : (void *)patch_kernel<T, S, SCHEME_DUGKS, REF>;
+}
+void *patch_fn_variant(int variant, int scheme, bool bnd, bool ref) { LBFV_PICK(patch_fn, variant, ref, scheme, bnd) }
 #undef LBFV_PICK
 template <typename T, typename S, bool BND>
 void *batch_fn_b(int scheme, bool two, bool pairs) {
@@ -400,6 +428,118 @@ bool has_boundary(const HostCase &h) { return !(h.periodic_x() && h.periodic_y()
 // the FP32 step kernels with the reference-velocity terms: only while a reference velocity is set
 bool ref_terms(const HostCase &h) { return !is_f64(h.variant) && (h.u0[0] != 0.0 || h.u0[1] != 0.0); }
 
+// ------------------------------------------------------------------ patches
+// Widest extent, ghost and halo cells included, of `parts` patches along an axis of n cells.
+// Patches within a halo of a non-periodic side are cut off by it (at most 9 of them per end),
+// the others differ in length only (patch r is the first short one).
+int patch_extent(int n, bool periodic, int parts, int halo) {
+    const int q = n / parts, r = n % parts;
+    auto extent = [&](int p) {
+        const int o0 = p * q + std::min(p, r), o1 = o0 + q + (p < r ? 1 : 0);
+        const int lo = periodic ? o0 - halo : std::max(o0 - halo, -1);
+        const int hi = periodic ? o1 + halo : std::min(o1 + halo, n + 1);
+        return hi - lo;
+    };
+    int w = std::max(extent(r), extent(std::max(r - 1, 0)));
+    for (int p = 0; p < std::min(parts, 10); ++p) w = std::max(w, std::max(extent(p), extent(parts - 1 - p)));
+    return w;
+}
+// Fewest patches along an axis whose extent fits `cap` cells (0: none does).
+int patch_parts(int n, bool periodic, int halo, int cap) {
+    if (!periodic && n + 2 <= cap) return 1;
+    // an end patch holds a ghost cell and one halo, the others two halos
+    const int edge = cap - halo - (periodic ? halo : 1), inner = cap - 2 * halo;
+    if (edge < 1) return 0;
+    const int last = inner < 1 ? std::min(n, 2) : std::min(n, (n + inner - 1) / inner);
+    for (int parts = std::max(1, (n + edge - 1) / edge); parts <= last; ++parts)
+        if (patch_extent(n, periodic, parts, halo) <= cap) return parts;
+    return 0;
+}
+constexpr int PATCH_HALO = 8;   // most steps per launch of the patch form
+// Largest mesh that takes the patch form where no launch shape was set.  Against one-step
+// marches of the default shape, us per step (DUGKS and BKG in FP64, then in FP32): 64^2 vortex
+// 1.7 / 1.4 / 1.5 / 1.2 against 11.6 / 8.9 / 10.6 / 8.4, 512^2 vortex 11.3 / 6.6 / 6.4 / 4.2
+// against 22.2 / 19.7 / 19.2 / 14.8, 512^2 cavity 13.1 / 16.6 / 7.9 / 6.5 against 32 / 28 / 28 /
+// 24; the 768^2 vortex is lost (30 against 27).
+constexpr int64_t PATCH_CELLS = 1 << 18;
+// Largest mesh on which the autotuner tries it: its fastest marches (two to four steps per
+// launch) pass the patch form between 200^2 and 450^2 cells.
+constexpr int64_t PATCH_TRIAL_CELLS = 1 << 20;
+
+// Patches of at most 64 / per_wave columns and waves x per_wave rows with the given halo.
+bool plan_patch(const HostCase &h, int per_wave, int waves, int halo, PatchPlan &p) {
+    PatchGrid &g = p.g;
+    g.halo = halo;
+    p.waves = 0;
+    p.per_wave = per_wave;
+    p.max_waves = waves;
+    if (h.plane * (int64_t)h.esize >= (1ll << 31)) return false;   // 32-bit offsets within a plane
+    if ((h.periodic_x() && h.nx <= halo) || (h.periodic_y() && h.ny <= halo)) return false;   // the halo wraps once
+    g.npx = patch_parts(h.nx, h.periodic_x(), halo, 64 / per_wave);
+    g.npy = g.npx ? patch_parts(h.ny, h.periodic_y(), halo, waves * per_wave) : 0;
+    if (!g.npy) return false;
+    g.tw = patch_extent(h.nx, h.periodic_x(), g.npx, halo);
+    g.fit = 64 / g.tw;
+    g.qx = h.nx / g.npx;
+    g.rx = h.nx % g.npx;
+    g.qy = h.ny / g.npy;
+    g.ry = h.ny % g.npy;
+    p.waves = (patch_extent(h.ny, h.periodic_y(), g.npy, halo) + g.fit - 1) / g.fit;
+    return true;
+}
+
+// What the cost model needs of the device: CUs, and the workgroups of a patch kernel that fit
+// on a CU with at most 4 and at most 8 waves each.  A workgroup's waves go round the four SIMDs
+// from the first one on, so that its share of a SIMD is 1 or 2 waves whatever the others hold.
+struct PatchDevice {
+    int cus = 256;
+    int fit[2] = {1, 1};
+};
+PatchDevice patch_device(const HostCase &h, void *fn) {
+    PatchDevice d;
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
+        d.cus = n;
+    for (int k = 0; k < 2; ++k) {
+        const int lanes = 256 * (k + 1);
+        const size_t lds = (size_t)PATCH_LDS * lanes * (is_f64(h.variant) ? 8 : 4);
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, lanes, lds) == hipSuccess && n > 0) d.fit[k] = n;
+        else (void)hipGetLastError();
+    }
+    return d;
+}
+
+// us per step of a plan, from timings on gfx950 (meshes of 32^2 to 448^2, both schemes and
+// precisions, every halo and workgroup size).  A launch costs 1.4 us, and per round of resident
+// workgroups 2 us for addresses, loads and stores and, for each step, a part that one wave alone
+// cannot hide (barriers, dependent arithmetic; 0.65 us more where patches hold ghost cells) and a
+// part per resident wave of a SIMD.
+double patch_cost(const HostCase &h, const PatchDevice &d, const PatchPlan &p, int scheme) {
+    const int64_t groups = (int64_t)p.g.npx * p.g.npy;
+    const int per_cu = (int)((groups + d.cus - 1) / d.cus), fit = d.fit[p.waves > 4];
+    const int waves = std::min(per_cu, fit) * ((p.waves + 3) / 4);   // resident per SIMD
+    const bool bkg = scheme == SCHEME_BKG, f64 = is_f64(h.variant);
+    const double alone = (f64 ? (bkg ? 0.55 : 0.3) : 0.35) + (has_boundary(h) ? 0.65 : 0.0);
+    const double each = f64 ? (bkg ? 0.33 : 0.8) : (bkg ? 0.33 : 0.6);
+    const int rounds = (per_cu + fit - 1) / fit;
+    return (1.4 + rounds * (2.0 + p.g.halo * (alone + each * waves))) / p.g.halo;
+}
+
+// The cheapest plan of the cost model with a halo in [lo, hi] (waves = 0: the mesh takes none).
+PatchPlan best_patch_plan(const HostCase &h, const PatchDevice &d, int scheme, int lo = 1, int hi = PATCH_HALO) {
+    PatchPlan best, p;
+    best.g.halo = lo;
+    for (int halo = lo; halo <= hi; ++halo)
+        for (int per_wave = 1; per_wave <= 6; ++per_wave)
+            for (int waves : {2, 4, 8}) {
+                if (!plan_patch(h, per_wave, waves, halo, p)) continue;
+                p.cost = patch_cost(h, d, p, scheme);
+                if (!best.waves || p.cost < best.cost) best = p;
+            }
+    return best;
+}
+
 // Kernel arguments of one step launch, in a form usable by hipLaunchKernel and by
 // graph kernel nodes.
 struct StepArgs {
@@ -407,6 +547,8 @@ struct StepArgs {
     StepParams<float> pf;
     const void *pptr = nullptr;   // device copy of the parameters, for kernels that take a pointer
     int parity, rows, nstrips, nwork;
+    int steps;                    // patch form: steps of the launch and the patches
+    PatchGrid grid;
     void *args[5];
     void bind(bool f64) {
         args[0] = f64 ? (void *)&pd : (void *)&pf;
@@ -414,6 +556,12 @@ struct StepArgs {
         args[2] = &rows;
         args[3] = &nstrips;
         args[4] = &nwork;
+    }
+    void bind_patch(const PatchGrid &g, int n) {
+        grid = g;
+        steps = n;
+        args[2] = &steps;
+        args[3] = &grid;
     }
 };
 
@@ -605,6 +753,7 @@ int ensure_metrics(lbfv_ctx *c, double ext[4]) {
         if (!h.sides_set()) return c->fail(LBFV_ESTATE, "all four sides must be set");
         HIPCHK(upload_metrics(h, ext, c->stream));
         drop_graphs(c);
+        c->plan[0] = c->plan[1] = PatchPlan();   // (the patches depend on the kinds of sides)
     }
     return LBFV_OK;
 }
@@ -614,6 +763,35 @@ void current_ext(const HostCase &h, double ext[4]) {
     std::vector<double> m, s;
     axis_metrics(h.xf, h.periodic_x(), h.dt, h.c, m, ext[SIDE_W], ext[SIDE_E], s);
     axis_metrics(h.yf, h.periodic_y(), h.dt, h.c, m, ext[SIDE_S], ext[SIDE_N], s);
+}
+
+void *patch_kernel_of(const lbfv_ctx *c, int scheme) {
+    return patch_fn_variant(c->hc.variant, scheme, has_boundary(c->hc), ref_terms(c->hc));
+}
+// the patches of a scheme's kernels, planned on first use
+PatchPlan &patch_plan(lbfv_ctx *c, int scheme) {
+    PatchPlan &p = c->plan[scheme == SCHEME_BKG];
+    if (!p.g.halo) p = best_patch_plan(c->hc, patch_device(c->hc, patch_kernel_of(c, scheme)), scheme);
+    return p;
+}
+// Whether the patch form advances the context (its metrics are up to date): asked for by the
+// autotuner, or by the size of the mesh where no shape was set.  A stream under capture gets
+// marches: an even number of one-step launches leaves the state in the buffer it started from,
+// which a program that replays what it captured relies on.
+bool use_patch(lbfv_ctx *c, int scheme) {
+    if (c->form == FORM_MARCH) return false;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) (void)hipGetLastError();
+    else if (capture != hipStreamCaptureStatusNone) return false;
+    const HostCase &h = c->hc;
+    if (c->form == FORM_AUTO && (int64_t)h.nx * h.ny > PATCH_CELLS) return false;
+    return patch_plan(c, scheme).waves > 0;
+}
+// grid, workgroup and LDS of a patch launch
+void patch_dims(const lbfv_ctx *c, const PatchPlan &p, dim3 &grid, dim3 &block, unsigned &lds) {
+    grid = dim3(p.g.npx * p.g.npy);
+    block = dim3(64 * p.waves);
+    lds = (unsigned)(PATCH_LDS * 64 * p.waves * (is_f64(c->hc.variant) ? 8 : 4));
 }
 
 // a launch of two steps with the pair-of-waves form
@@ -699,6 +877,23 @@ int launch_args(lbfv_ctx *c, int scheme, int parity, const double ext[4], const 
     return LBFV_OK;
 }
 
+// one launch of `steps` time steps of the patch form
+int launch_patch(lbfv_ctx *c, int scheme, int parity, const double ext[4], int steps) {
+    HostCase &h = c->hc;
+    const PatchPlan &p = patch_plan(c, scheme);
+    StepShape sh = step_shape(h, 1, 1);
+    StepArgs a;
+    int st = launch_args(c, scheme, parity, ext, sh, a);
+    if (st) return st;
+    a.bind_patch(p.g, steps);
+    dim3 grid, block;
+    unsigned lds;
+    patch_dims(c, p, grid, block, lds);
+    HIPCHK(hipLaunchKernel(patch_kernel_of(c, scheme), grid, block, a.args, lds,
+                           c->stream));
+    return LBFV_OK;
+}
+
 int launch_one(lbfv_ctx *c, int scheme, int parity, const double ext[4], int tb = 1) {
     HostCase &h = c->hc;
     StepShape sh = step_shape(h, c->rows, c->wpb);
@@ -711,9 +906,10 @@ int launch_one(lbfv_ctx *c, int scheme, int parity, const double ext[4], int tb 
     return LBFV_OK;
 }
 
-int build_graph(lbfv_ctx *c, int scheme, int parity0, const double ext[4], int tb = 1) {
+// a graph of gsteps launches of tb steps each, in the patch form or as marches
+int build_graph(lbfv_ctx *c, int scheme, int parity0, const double ext[4], int tb, bool patch) {
     HostCase &h = c->hc;
-    StepShape sh = step_shape(h, c->rows, c->wpb);
+    StepShape sh = step_shape(h, patch ? 1 : c->rows, c->wpb);
     hipGraph_t g;
     HIPCHK(hipGraphCreate(&g, 0));
     hipGraphNode_t prev = nullptr;
@@ -726,9 +922,15 @@ int build_graph(lbfv_ctx *c, int scheme, int parity0, const double ext[4], int t
         }
         hipKernelNodeParams kp;
         memset(&kp, 0, sizeof(kp));
-        kp.func = launch_fn(c, scheme, tb);
-        launch_dims(c, tb, sh, kp.gridDim, kp.blockDim);
-        kp.sharedMemBytes = 0;
+        if (patch) {
+            const PatchPlan &p = patch_plan(c, scheme);
+            a.bind_patch(p.g, tb);
+            kp.func = patch_kernel_of(c, scheme);
+            patch_dims(c, p, kp.gridDim, kp.blockDim, kp.sharedMemBytes);
+        } else {
+            kp.func = launch_fn(c, scheme, tb);
+            launch_dims(c, tb, sh, kp.gridDim, kp.blockDim);
+        }
         kp.kernelParams = a.args;
         kp.extra = nullptr;
         hipGraphNode_t node;
@@ -739,7 +941,8 @@ int build_graph(lbfv_ctx *c, int scheme, int parity0, const double ext[4], int t
         }
         prev = node;
     }
-    hipError_t e = hipGraphInstantiate(&c->gexec[scheme + 4 * (tb - 1)][parity0], g, nullptr, nullptr, 0);
+    hipError_t e = hipGraphInstantiate(&c->gexec[patch ? 16 + scheme : scheme + 4 * (tb - 1)][parity0], g, nullptr,
+                                       nullptr, 0);
     (void)hipGraphDestroy(g);
     if (e != hipSuccess) return c->fail(LBFV_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
     return LBFV_OK;
@@ -869,6 +1072,32 @@ const char *reference_conflict(const HostCase &h) {
     return nullptr;
 }
 
+// lbfv_set_time_block, the form of the launches left as it is
+int set_time_block(lbfv_ctx *c, int32_t steps) {
+    HostCase &h = c->hc;
+    if (steps < 1 || steps > 4) return c->fail(LBFV_EINVAL, "lbfv_set_time_block: steps must be 1 to 4");
+    if (steps >= 2 && !h.sides_set())
+        return c->fail(LBFV_EINVAL, "lbfv_set_time_block: set all four sides first");
+    if (steps >= 3 && has_boundary(h))
+        return c->fail(LBFV_EINVAL, "lbfv_set_time_block: 3 or 4 steps per launch need a doubly periodic mesh");
+    if (steps >= 3 && (h.nx < 2 * steps || h.ny < 2 * steps))
+        return c->fail(LBFV_EINVAL, "lbfv_set_time_block: 3 or 4 steps per launch need at least 2 x steps cells per side");
+    const int w = SLOTS - 2 * steps;   // 62, 60, 58 or 56 output columns per strip
+    if (w != h.strip) {
+        if (c->has_state) {
+            // move the current state into the other buffer in the new layout
+            int st = poll_check(c, true);
+            if (st) return st;
+            HIPCHK(relayout(h, h.cur, w, c->stream));
+            h.cur ^= 1;
+        }
+        h.set_strip(w);
+        drop_graphs(c);
+    }
+    h.tblock = steps;
+    return LBFV_OK;
+}
+
 int do_steps(lbfv_ctx *c, int scheme, int32_t n) {
     if (!c) return LBFV_EINVAL;
     if (n < 0) return c->fail(LBFV_EINVAL, "nsteps must be >= 0");
@@ -885,27 +1114,32 @@ int do_steps(lbfv_ctx *c, int scheme, int32_t n) {
     if (h.tblock >= 3 && has_boundary(h)) {
         // a side stopped being periodic: the chains of waves have no ghost cells, so the
         // mesh continues with two steps per launch
-        if ((st = lbfv_set_time_block(c, 2))) return st;
+        if ((st = set_time_block(c, 2))) return st;
     }
     current_ext(h, ext);
-    if (c->rows <= 0) c->rows = default_rows(h, scheme, c->wpb);
+    const bool patch = use_patch(c, scheme);
+    if (!patch && c->rows <= 0) c->rows = default_rows(h, scheme, c->wpb);
     // tblock steps per launch; the steps left over make one launch of fewer steps, in the
-    // same strip layout (every narrower march fits a wider halo's strip)
-    const int per = h.tblock;
+    // same strip layout (every narrower march fits a wider halo's strip).  The patch form
+    // takes up to its halo width of steps per launch.
+    const int per = patch ? patch_plan(c, scheme).g.halo : h.tblock;
+    auto launch = [&](int steps) {
+        return patch ? launch_patch(c, scheme, h.cur, ext, steps) : launch_one(c, scheme, h.cur, ext, steps);
+    };
     while (n > 0) {
         int seg = n;
         if (c->check_every > 0) {
             // the check comes at the first launch boundary at or after check_every steps,
             // so that a check never splits a launch of `per` steps into shorter ones
             int64_t to_check = std::max<int64_t>(c->check_every - (c->steps - c->steps_at_check), 1);
-            to_check = (to_check + per - 1) / per * per;
+            if (!patch) to_check = (to_check + per - 1) / per * per;
             seg = (int)std::min<int64_t>(seg, to_check);
         }
         int left = seg;
         while (left >= per * c->gsteps) {
-            hipGraphExec_t &g = c->gexec[scheme + 4 * (per - 1)][h.cur];
+            hipGraphExec_t &g = c->gexec[patch ? 16 + scheme : scheme + 4 * (per - 1)][h.cur];
             if (!g) {
-                st = build_graph(c, scheme, h.cur, ext, per);
+                st = build_graph(c, scheme, h.cur, ext, per, patch);
                 if (st) return st;
             }
             HIPCHK(hipGraphLaunch(g, c->stream));
@@ -913,12 +1147,12 @@ int do_steps(lbfv_ctx *c, int scheme, int32_t n) {
             left -= per * c->gsteps;
         }
         for (; left >= per; left -= per) {
-            st = launch_one(c, scheme, h.cur, ext, per);
+            st = launch(per);
             if (st) return st;
             h.cur ^= 1;
         }
         if (left > 0) {
-            st = launch_one(c, scheme, h.cur, ext, left);
+            st = launch(left);
             if (st) return st;
             h.cur ^= 1;
         }
@@ -1384,28 +1618,9 @@ int lbfv_residual(lbfv_ctx *c, double *r) {
 
 int lbfv_set_time_block(lbfv_ctx *c, int32_t steps) {
     if (!c) return LBFV_EINVAL;
-    HostCase &h = c->hc;
-    if (steps < 1 || steps > 4) return c->fail(LBFV_EINVAL, "lbfv_set_time_block: steps must be 1 to 4");
-    if (steps >= 2 && !h.sides_set())
-        return c->fail(LBFV_EINVAL, "lbfv_set_time_block: set all four sides first");
-    if (steps >= 3 && has_boundary(h))
-        return c->fail(LBFV_EINVAL, "lbfv_set_time_block: 3 or 4 steps per launch need a doubly periodic mesh");
-    if (steps >= 3 && (h.nx < 2 * steps || h.ny < 2 * steps))
-        return c->fail(LBFV_EINVAL, "lbfv_set_time_block: 3 or 4 steps per launch need at least 2 x steps cells per side");
-    const int w = SLOTS - 2 * steps;   // 62, 60, 58 or 56 output columns per strip
-    if (w != h.strip) {
-        if (c->has_state) {
-            // move the current state into the other buffer in the new layout
-            int st = poll_check(c, true);
-            if (st) return st;
-            HIPCHK(relayout(h, h.cur, w, c->stream));
-            h.cur ^= 1;
-        }
-        h.set_strip(w);
-        drop_graphs(c);
-    }
-    h.tblock = steps;
-    return LBFV_OK;
+    int st = set_time_block(c, steps);
+    if (!st) c->form = FORM_MARCH;
+    return st;
 }
 
 int lbfv_get_time_block(const lbfv_ctx *c, int32_t *steps) {
@@ -1458,6 +1673,7 @@ int lbfv_set_tile(lbfv_ctx *c, int32_t rows, int32_t wpb) {
         return c->fail(LBFV_EINVAL, "lbfv_set_tile: rows >= 1, waves per block 1, 2 or 4");
     if (rows > 0) c->rows = rows;
     if (wpb > 0) c->wpb = wpb;
+    if (rows > 0 || wpb > 0) c->form = FORM_MARCH;
     drop_graphs(c);
     return LBFV_OK;
 }
@@ -1473,6 +1689,7 @@ int lbfv_set_wave_pairs(lbfv_ctx *c, int32_t on) {
     if (!c) return LBFV_EINVAL;
     if (on != 0 && on != 1) return c->fail(LBFV_EINVAL, "lbfv_set_wave_pairs: 0 or 1");
     c->pairs = on;
+    c->form = FORM_MARCH;
     drop_graphs(c);
     return LBFV_OK;
 }
@@ -1510,7 +1727,9 @@ std::string tune_key(const HostCase &h, int scheme) {
     return s.str();
 }
 
-bool cache_lookup(const char *path, const std::string &key, int &rows, int &wpb, double &ms, int &tb, int &pairs) {
+// patch: halo, per_wave and max_waves of a plan of the patch form (halo 0: marches)
+bool cache_lookup(const char *path, const std::string &key, int &rows, int &wpb, double &ms, int &tb, int &pairs,
+                  std::array<int, 3> &patch) {
     if (!path) return false;
     std::ifstream in(path);
     std::string line;
@@ -1523,6 +1742,10 @@ bool cache_lookup(const char *path, const std::string &key, int &rows, int &wpb,
             if (t >> r >> w >> m) {
                 if (!(t >> k) || k < 1 || k > 4) k = 1;
                 if (!(t >> pr) || (pr != 0 && pr != 1)) pr = 0;
+                patch = {0, 0, 0};
+                if (!(t >> patch[0] >> patch[1] >> patch[2]) || patch[0] < 1 || patch[0] > PATCH_HALO || patch[1] < 1 ||
+                    patch[1] > 64 || patch[2] < 1 || patch[2] > PATCH_WAVES)
+                    patch = {0, 0, 0};
                 rows = r;
                 wpb = w;
                 ms = m;
@@ -1535,10 +1758,13 @@ bool cache_lookup(const char *path, const std::string &key, int &rows, int &wpb,
     return found;
 }
 
-void cache_store(const char *path, const std::string &key, int rows, int wpb, double ms, int tb, int pairs) {
+void cache_store(const char *path, const std::string &key, int rows, int wpb, double ms, int tb, int pairs,
+                 const std::array<int, 3> &patch) {
     if (!path) return;
     std::ofstream out(path, std::ios::app);
-    out << key << "|" << rows << " " << wpb << " " << ms << " " << tb << " " << pairs << "\n";
+    out << key << "|" << rows << " " << wpb << " " << ms << " " << tb << " " << pairs;
+    if (patch[0]) out << " " << patch[0] << " " << patch[1] << " " << patch[2];
+    out << "\n";
 }
 
 }  // namespace
@@ -1554,18 +1780,26 @@ extern "C" int lbfv_autotune(lbfv_ctx *c, int scheme, int32_t trial_steps, const
     HostCase &h = c->hc;
     const std::string key = tune_key(h, scheme);
     int rows, wpb, tb, pairs;
+    std::array<int, 3> patch;
     double ms;
-    // (an entry of the same size class whose time block this mesh cannot take is ignored)
-    if (cache_lookup(path, key, rows, wpb, ms, tb, pairs) &&
+    // (an entry of the same size class whose time block or patches this mesh cannot take is ignored)
+    if (cache_lookup(path, key, rows, wpb, ms, tb, pairs, patch) &&
         (tb < 3 || (!has_boundary(h) && std::min(h.nx, h.ny) >= 2 * tb))) {
-        int st = lbfv_set_time_block(c, tb);
-        if (st) return st;
-        c->rows = std::min(rows, h.ny);
-        c->wpb = wpb;
-        c->pairs = pairs;
-        drop_graphs(c);
-        if (best_ms) *best_ms = ms;
-        return LBFV_OK;
+        PatchPlan plan;
+        if (!patch[0] || plan_patch(h, patch[1], patch[2], patch[0], plan)) {
+            double ext[4];
+            int st = ensure_metrics(c, ext);   // (it drops the plans of other sides)
+            if (!st) st = set_time_block(c, tb);
+            if (st) return st;
+            c->rows = std::min(rows, h.ny);
+            c->wpb = wpb;
+            c->pairs = pairs;
+            c->form = patch[0] ? FORM_PATCH : FORM_MARCH;
+            if (patch[0]) c->plan[scheme == SCHEME_BKG] = plan;
+            drop_graphs(c);
+            if (best_ms) *best_ms = ms;
+            return LBFV_OK;
+        }
     }
     // save the state; trials step it (and may move it between strip layouts)
     void *save = nullptr;
@@ -1582,8 +1816,9 @@ extern "C" int lbfv_autotune(lbfv_ctx *c, int scheme, int32_t trial_steps, const
     HIPCHK(hipEventCreate(&e1));
     c->check_every = 0;
     int best_r = 0, best_w = 0, best_t = 1, best_p = 0;
-    const int saved_pairs = c->pairs;
-    double best = INFINITY;
+    int one_r = 0, one_w = 0;                 // the fastest march of one step per launch
+    double best = INFINITY, best_one = INFINITY;
+    const int saved_pairs = c->pairs, saved_form = c->form;
     int st = LBFV_OK;
     // candidate shapes: (time block, pair of waves per item, rows, waves per block)
     std::vector<std::array<int, 4>> cands;
@@ -1619,24 +1854,29 @@ extern "C" int lbfv_autotune(lbfv_ctx *c, int scheme, int32_t trial_steps, const
         }
     std::sort(cands.begin(), cands.end());
     cands.erase(std::unique(cands.begin(), cands.end()), cands.end());
-    for (const auto &cand : cands) {
-        if ((st = lbfv_set_time_block(c, cand[0]))) break;
-        c->pairs = cand[1];
-        c->rows = cand[2];
-        c->wpb = cand[3];
+    // one trial of the shape set on the context: ms per step
+    auto trial = [&](double &per) {
         drop_graphs(c);
-        if ((st = do_steps(c, scheme, 2))) break;   // warm-up
+        int ts = do_steps(c, scheme, 2);   // warm-up
+        if (ts) return ts;
         hipError_t he = hipEventRecord(e0, c->stream);
-        if (he == hipSuccess && (st = do_steps(c, scheme, trial_steps))) break;
+        if (he == hipSuccess && (ts = do_steps(c, scheme, trial_steps))) return ts;
         float t = 0;
         if (he == hipSuccess) he = hipEventRecord(e1, c->stream);
         if (he == hipSuccess) he = hipEventSynchronize(e1);
         if (he == hipSuccess) he = hipEventElapsedTime(&t, e0, e1);
-        if (he != hipSuccess) {
-            st = c->fail(LBFV_EHIP, std::string("autotune timing: ") + hipGetErrorString(he));
-            break;
-        }
-        const double per = t / trial_steps;
+        if (he != hipSuccess) return c->fail(LBFV_EHIP, std::string("autotune timing: ") + hipGetErrorString(he));
+        per = t / trial_steps;
+        return (int)LBFV_OK;
+    };
+    c->form = FORM_MARCH;
+    for (const auto &cand : cands) {
+        if ((st = set_time_block(c, cand[0]))) break;
+        c->pairs = cand[1];
+        c->rows = cand[2];
+        c->wpb = cand[3];
+        double per;
+        if ((st = trial(per))) break;
         if (per < best) {
             best = per;
             best_t = cand[0];
@@ -1644,6 +1884,37 @@ extern "C" int lbfv_autotune(lbfv_ctx *c, int scheme, int32_t trial_steps, const
             best_r = cand[2];
             best_w = cand[3];
         }
+        if (cand[0] == 1 && per < best_one) {
+            best_one = per;
+            one_r = cand[2];
+            one_w = cand[3];
+        }
+    }
+    // the patch form on small meshes: the cost model's best plan at each halo width, unless the
+    // model puts it far behind its best one
+    PatchPlan best_plan;
+    if (!st && (int64_t)h.nx * h.ny <= PATCH_TRIAL_CELLS && !(st = set_time_block(c, 1))) {
+        const PatchDevice dev = patch_device(h, patch_kernel_of(c, scheme));
+        const double limit = 1.4 * best_patch_plan(h, dev, scheme).cost;
+        c->form = FORM_PATCH;
+        for (int halo = 1; halo <= PATCH_HALO && !st; ++halo) {
+            const PatchPlan p = best_patch_plan(h, dev, scheme, halo, halo);
+            if (!p.waves || p.cost > limit) continue;
+            c->plan[scheme == SCHEME_BKG] = p;
+            double per;
+            if ((st = trial(per))) break;
+            if (per < best) {
+                best = per;
+                best_plan = p;
+            }
+        }
+    }
+    if (best_plan.waves) {
+        // the march controls then hold the fastest march of the same (one-step) layout
+        best_t = 1;
+        best_p = 0;
+        best_r = one_r;
+        best_w = one_w;
     }
     // restore the saved state in its own layout, then move it to the chosen one
     h.set_strip(saved_strip);
@@ -1659,14 +1930,18 @@ extern "C" int lbfv_autotune(lbfv_ctx *c, int scheme, int32_t trial_steps, const
     c->steps_at_check = saved_at;
     c->check_every = saved_check;
     c->pairs = saved_pairs;
+    c->form = saved_form;
+    c->plan[scheme == SCHEME_BKG] = best_plan;   // (none: planned again on use)
     drop_graphs(c);
     if (st) return st;
-    if ((st = lbfv_set_time_block(c, best_t))) return st;
+    if ((st = set_time_block(c, best_t))) return st;
     c->rows = best_r;
     c->wpb = best_w;
     c->pairs = best_p;
+    c->form = best_plan.waves ? FORM_PATCH : FORM_MARCH;
     drop_graphs(c);
-    cache_store(path, key, best_r, best_w, best, best_t, best_p);
+    cache_store(path, key, best_r, best_w, best, best_t, best_p,
+                {best_plan.waves ? best_plan.g.halo : 0, best_plan.per_wave, best_plan.max_waves});
     if (best_ms) *best_ms = best;
     return LBFV_OK;
 }
