@@ -191,7 +191,7 @@ int lbfv_totals_device(lbfv_ctx *ctx, double *dev_out);
 /* Execution shape of the step kernel: rows of the row block one wavefront marches
  * through, and wavefronts per workgroup (1, 2 or 4).  0 keeps the current value.
  * A context on which no shape has been set (by this call, lbfv_set_wave_pairs,
- * lbfv_set_time_block or lbfv_autotune) advances a small mesh (at most 2^18 cells) in the
+ * lbfv_set_time_block or lbfv_autotune) advances a small mesh (at most 2^20 cells) in the
  * patch form instead: rectangular patches with one cell per lane, up to 8 steps per launch,
  * each patch recomputing a halo.  The results are those of one-step launches bit for bit, in
  * every storage (16-bit storage is rounded after every step); checks fall due exactly at
@@ -237,9 +237,9 @@ int lbfv_get_reference_velocity(const lbfv_ctx *ctx, double *ux, double *uy);
 /* Autotuner: times the candidate shapes for `scheme` on this context (the state is
  * saved and restored; on small meshes the patch form of lbfv_set_tile is a candidate, and
  * where it wins the march controls hold the fastest march of one step per launch), keeps
- * the fastest, and records it in a cache file keyed by (gfx arch, scheme, precision, storage, time block, mesh size class).  cache_path NULL: the
- * environment variable LBFV_TUNE_CACHE, else no file.  A cached entry is used
- * without timing.  best_ms (nullable) receives the time per step of the choice. */
+ * the fastest, and records it in a cache file keyed by (gfx arch, scheme, precision,
+ * storage, time block, mesh size class).  cache_path NULL: the environment variable
+ * LBFV_TUNE_CACHE, else no file.  A cached entry is used without timing.  best_ms (nullable) receives the time per step of the choice. */
 int lbfv_autotune(lbfv_ctx *ctx, int scheme, int32_t trial_steps, const char *cache_path,
                   double *best_ms);
 
@@ -276,7 +276,9 @@ int lbfv_batch_moments(lbfv_batch *b, int32_t case_id, double *rho, double *ux, 
  * non-finite check, used to map the stable range of (CFL, dt/tau) (Sec. 3.2). */
 int lbfv_batch_nonfinite(lbfv_batch *b, int32_t *count);
 /* Graph length K (default 100) and rows per row block of the work list (default 8); 0
- * keeps the current value. */
+ * keeps the current value.  A batch on which no shape has been set (rows, time block, grid
+ * form, wave pairs or the autotuner) and whose meshes have at most 2^18 cells each advances
+ * in the patch form of lbfv_set_tile: the same bits, up to 8 steps per launch. */
 int lbfv_batch_set_shape(lbfv_batch *b, int32_t graph_steps, int32_t rows);
 int lbfv_batch_get_shape(const lbfv_batch *b, int32_t *graph_steps, int32_t *rows);
 /* Grid form of the batch's launches: 0 (default) launches the waves that fit on the device
@@ -303,7 +305,8 @@ int lbfv_batch_get_time_block(const lbfv_batch *b, int32_t *steps);
  * list (2, 4, ..., 64 and the three a cost model of whole rounds of resident waves ranks
  * best) and two grid forms (the resident waves walking the list, or one wave per item) for
  * `scheme`, each as a replay of a graph of trial_steps launches after one warm-up replay;
- * keeps the fastest, and restores every case's state and the step parity (the trial steps
+ * so too the patch form, where it comes near (if it wins, the march controls hold the fastest
+ * march of one step per launch); keeps the fastest, and restores every case's state and the step parity (the trial steps
  * leave no trace).  Needs a device copy of the whole state for its
  * duration (ENOMEM otherwise).  best_ms (nullable) receives the time per step of the
  * choice.  EINVAL for an unknown scheme or trial_steps < 1. */

@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstring>
 #include <fstream>
+#include <map>
 #include <mutex>
 #include <sstream>
 #include <string>
@@ -138,7 +139,16 @@ struct lbfv_batch {
     bool bnd = false;                // some case has a non-periodic side
     int slots[3][2] = {{0, 0}, {0, 0}, {0, 0}};   // resident work items of the batch kernels: one step, two
                                                    // steps, two steps with pairs of waves; per scheme
-    hipGraphExec_t gexec[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
+    hipGraphExec_t gexec[4][2] = {};              // per scheme (+2: the patch form) and starting buffer
+    int form = FORM_AUTO;
+    // the patch form, per scheme: halo and waves of all patches (halo 0: not planned yet; waves
+    // 0: the batch takes none), their count and what the cost model gives them, us per step
+    struct Patches {
+        int halo = 0, waves = 0, count = 0;
+        double cost = 0.0;
+        PatchGrid *d_grids = nullptr;
+        PatchItem *d_items = nullptr;
+    } patches[2];
     bool has_state = false;
     std::string last_error;
     int fail(int status, const std::string &msg) {
@@ -413,6 +423,22 @@ template <typename T, typename S>
 void *batch_fn(int scheme, bool bnd, bool two, bool pairs) {
     return bnd ? batch_fn_b<T, S, true>(scheme, two, pairs) : batch_fn_b<T, S, false>(scheme, two, pairs);
 }
+template <typename T, typename S>
+void *batch_patch_fn(int scheme, bool bnd) {
+    if (bnd)
+        return scheme == SCHEME_DUGKS ? (void *)batch_patch_kernel<T, S, SCHEME_DUGKS, true>
+                                      : (void *)batch_patch_kernel<T, S, SCHEME_BKG, true>;
+    return scheme == SCHEME_DUGKS ? (void *)batch_patch_kernel<T, S, SCHEME_DUGKS, false>
+                                  : (void *)batch_patch_kernel<T, S, SCHEME_BKG, false>;
+}
+void *batch_patch_fn_variant(int variant, int scheme, bool bnd) {
+    switch (variant) {
+    case V_F64: return batch_patch_fn<double, double>(scheme, bnd);
+    case V_F32: return batch_patch_fn<float, float>(scheme, bnd);
+    case V_BF16: return batch_patch_fn<float, __bf16>(scheme, bnd);
+    default: return batch_patch_fn<float, _Float16>(scheme, bnd);
+    }
+}
 // two: two time steps per launch (the cases in the 60-column strip layout); pairs: with a
 // pair of waves per work item
 void *batch_fn_variant(int variant, int scheme, bool bnd, bool two, bool pairs = false) {
@@ -458,10 +484,15 @@ int patch_parts(int n, bool periodic, int halo, int cap) {
 constexpr int PATCH_HALO = 8;   // most steps per launch of the patch form
 // Largest mesh that takes the patch form where no launch shape was set.  Against one-step
 // marches of the default shape, us per step (DUGKS and BKG in FP64, then in FP32): 64^2 vortex
-// 1.7 / 1.4 / 1.5 / 1.2 against 11.6 / 8.9 / 10.6 / 8.4, 512^2 vortex 11.3 / 6.6 / 6.4 / 4.2
-// against 22.2 / 19.7 / 19.2 / 14.8, 512^2 cavity 13.1 / 16.6 / 7.9 / 6.5 against 32 / 28 / 28 /
-// 24; the 768^2 vortex is lost (30 against 27).
-constexpr int64_t PATCH_CELLS = 1 << 18;
+// 1.7 / 1.3 / 1.4 / 1.2 against 11.6 / 8.9 / 10.6 / 8.4, 512^2 cavity 13 / 8 / 7 / 5 against 32 / 28
+// / 28 / 24, 1024^2 vortex 30 / 23 / 20 / 15 against 50 / 49 / 30 / 28, 1024^2 cavity 39 / 26 / 24 /
+// 16 against 63 / 54 / 37 / 34.
+constexpr int64_t PATCH_CELLS = 1 << 20;
+// Largest mesh of a batch that takes it where no launch shape was set.  Against one-step marches
+// of the default shape, us per step (DUGKS and BKG in FP64, then in FP32): 100 cavities of 64^2
+// 19 / 14 / 12 / 9 against 41 / 32 / 22 / 20, 6 of 512^2 59 / 41 / 36 / 25 against 75 / 65 / 56 / 38;
+// 96 uneven cases of 64^2 to 512^2 in FP32 210 / 154 against 213 / 208.
+constexpr int64_t BATCH_PATCH_CELLS = 1 << 18;
 // Largest mesh on which the autotuner tries it: its fastest marches (two to four steps per
 // launch) pass the patch form between 200^2 and 450^2 cells.
 constexpr int64_t PATCH_TRIAL_CELLS = 1 << 20;
@@ -495,7 +526,7 @@ struct PatchDevice {
     int cus = 256;
     int fit[2] = {1, 1};
 };
-PatchDevice patch_device(const HostCase &h, void *fn) {
+PatchDevice patch_device(bool f64, void *fn) {
     PatchDevice d;
     int dev = 0, n = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
@@ -503,27 +534,35 @@ PatchDevice patch_device(const HostCase &h, void *fn) {
         d.cus = n;
     for (int k = 0; k < 2; ++k) {
         const int lanes = 256 * (k + 1);
-        const size_t lds = (size_t)PATCH_LDS * lanes * (is_f64(h.variant) ? 8 : 4);
+        const size_t lds = (size_t)PATCH_LDS * lanes * (f64 ? 8 : 4);
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, lanes, lds) == hipSuccess && n > 0) d.fit[k] = n;
         else (void)hipGetLastError();
     }
     return d;
 }
 
-// us per step of a plan, from timings on gfx950 (meshes of 32^2 to 448^2, both schemes and
-// precisions, every halo and workgroup size).  A launch costs 1.4 us, and per round of resident
-// workgroups 2 us for addresses, loads and stores and, for each step, a part that one wave alone
-// cannot hide (barriers, dependent arithmetic; 0.65 us more where patches hold ghost cells) and a
-// part per resident wave of a SIMD.
-double patch_cost(const HostCase &h, const PatchDevice &d, const PatchPlan &p, int scheme) {
-    const int64_t groups = (int64_t)p.g.npx * p.g.npy;
-    const int per_cu = (int)((groups + d.cus - 1) / d.cus), fit = d.fit[p.waves > 4];
-    const int waves = std::min(per_cu, fit) * ((p.waves + 3) / 4);   // resident per SIMD
-    const bool bkg = scheme == SCHEME_BKG, f64 = is_f64(h.variant);
-    const double alone = (f64 ? (bkg ? 0.55 : 0.3) : 0.35) + (has_boundary(h) ? 0.65 : 0.0);
-    const double each = f64 ? (bkg ? 0.33 : 0.8) : (bkg ? 0.33 : 0.6);
-    const int rounds = (per_cu + fit - 1) / fit;
-    return (1.4 + rounds * (2.0 + p.g.halo * (alone + each * waves))) / p.g.halo;
+// us per step of `groups` workgroups of at most 4 or 8 waves, `halo` steps per launch, from
+// timings on gfx950 (meshes of 32^2 to 1024^2 alone and in batches, both schemes and precisions,
+// every halo and workgroup size).  A launch costs 1.4 us.  Where all workgroups are resident at
+// once, or a CU takes one at a time, latency counts, per round: 1.6 us and 0.4 us per resident
+// wave of a SIMD for addresses, loads and stores, and per step a part that one wave alone cannot
+// hide (barriers, dependent arithmetic; 0.6 us more where patches hold ghost cells) and a part
+// per resident wave; within 15 %.  Otherwise the workgroups hide each other's waits and their
+// throughput counts, per wave of a SIMD: loads and stores and the steps' arithmetic, but at least
+// the time of its memory traffic.
+double patch_cost(bool f64, bool bkg, bool bnd, const PatchDevice &d, int64_t groups, int waves, int halo) {
+    const int per_cu = (int)((groups + d.cus - 1) / d.cus), fit = d.fit[waves > 4];
+    const int share = std::min(per_cu, fit) * (waves > 4 ? 2 : 1);   // resident waves of a SIMD
+    if (per_cu <= fit || fit == 1) {
+        const int rounds = (per_cu + fit - 1) / fit;
+        const double alone = (f64 ? (bkg ? 0.55 : 0.3) : 0.35) + (bnd ? 0.6 : 0.0);
+        const double each = f64 ? (bkg ? 0.33 : 0.75) : (bkg ? 0.2 : 0.5);
+        return (1.4 + rounds * (1.6 + 0.4 * share + halo * (alone + each * share))) / halo;
+    }
+    const double least = f64 ? (bkg ? 2.0 : 2.6) : (bkg ? 1.6 : 2.05);
+    const double load = f64 ? (bkg ? 1.4 : 1.7) : (bkg ? 0.85 : 0.7);
+    const double step = f64 ? (bkg ? 0.33 : 0.57) : (bkg ? 0.2 : 0.45);
+    return (1.4 + ((double)per_cu / fit + 0.3) * share * std::max(least, load + halo * step)) / halo;
 }
 
 // The cheapest plan of the cost model with a halo in [lo, hi] (waves = 0: the mesh takes none).
@@ -534,7 +573,8 @@ PatchPlan best_patch_plan(const HostCase &h, const PatchDevice &d, int scheme, i
         for (int per_wave = 1; per_wave <= 6; ++per_wave)
             for (int waves : {2, 4, 8}) {
                 if (!plan_patch(h, per_wave, waves, halo, p)) continue;
-                p.cost = patch_cost(h, d, p, scheme);
+                p.cost = patch_cost(is_f64(h.variant), scheme == SCHEME_BKG, has_boundary(h), d,
+                                    (int64_t)p.g.npx * p.g.npy, p.waves, halo);
                 if (!best.waves || p.cost < best.cost) best = p;
             }
     return best;
@@ -771,7 +811,7 @@ void *patch_kernel_of(const lbfv_ctx *c, int scheme) {
 // the patches of a scheme's kernels, planned on first use
 PatchPlan &patch_plan(lbfv_ctx *c, int scheme) {
     PatchPlan &p = c->plan[scheme == SCHEME_BKG];
-    if (!p.g.halo) p = best_patch_plan(c->hc, patch_device(c->hc, patch_kernel_of(c, scheme)), scheme);
+    if (!p.g.halo) p = best_patch_plan(c->hc, patch_device(is_f64(c->hc.variant), patch_kernel_of(c, scheme)), scheme);
     return p;
 }
 // Whether the patch form advances the context (its metrics are up to date): asked for by the
@@ -1894,7 +1934,7 @@ extern "C" int lbfv_autotune(lbfv_ctx *c, int scheme, int32_t trial_steps, const
     // model puts it far behind its best one
     PatchPlan best_plan;
     if (!st && (int64_t)h.nx * h.ny <= PATCH_TRIAL_CELLS && !(st = set_time_block(c, 1))) {
-        const PatchDevice dev = patch_device(h, patch_kernel_of(c, scheme));
+        const PatchDevice dev = patch_device(is_f64(h.variant), patch_kernel_of(c, scheme));
         const double limit = 1.4 * best_patch_plan(h, dev, scheme).cost;
         c->form = FORM_PATCH;
         for (int halo = 1; halo <= PATCH_HALO && !st; ++halo) {
@@ -2002,6 +2042,111 @@ int batch_build_items(lbfv_batch *b) {
     return LBFV_OK;
 }
 
+// ------------------------------------------------------------------ patches of a batch
+// Patches of at most 4 or 8 waves with one halo width for every case: of each kind of mesh the
+// fewest.  grids: one per case.  false if some case takes none.
+bool plan_batch_patches(const lbfv_batch *b, int max_waves, int halo, std::vector<PatchGrid> &grids, int &waves,
+                        int64_t &count) {
+    std::map<std::array<int, 4>, PatchPlan> kinds;
+    grids.clear();
+    waves = 0;
+    count = 0;
+    for (const auto &h : b->cases) {
+        PatchPlan &best = kinds[{h.nx, h.ny, h.periodic_x(), h.periodic_y()}];
+        for (int per_wave = best.waves ? 7 : 1; per_wave <= 6; ++per_wave) {
+            PatchPlan p;
+            if (!plan_patch(h, per_wave, max_waves, halo, p)) continue;
+            if (!best.waves || (int64_t)p.g.npx * p.g.npy < (int64_t)best.g.npx * best.g.npy) best = p;
+        }
+        if (!best.waves) return false;
+        grids.push_back(best.g);
+        waves = std::max(waves, best.waves);
+        count += (int64_t)best.g.npx * best.g.npy;
+    }
+    return count < (1 << 24);
+}
+void drop_patches(lbfv_batch::Patches &p) {
+    if (p.d_grids) (void)hipFree(p.d_grids);
+    if (p.d_items) (void)hipFree(p.d_items);
+    p = lbfv_batch::Patches();
+}
+// Put the patches of a halo width (0: the cost model's choice of it) and workgroup size in place;
+// without any that every case takes, waves stays 0.
+int make_patches(lbfv_batch *b, int scheme, int halo, int max_waves) {
+    lbfv_batch::Patches &out = b->patches[scheme];
+    drop_patches(out);
+    out.halo = std::max(halo, 1);
+    const bool f64 = is_f64(b->variant);
+    const PatchDevice dev = patch_device(f64, batch_patch_fn_variant(b->variant, scheme, b->bnd));
+    std::vector<PatchGrid> grids, best;
+    for (int hw = halo ? halo : 1; hw <= (halo ? halo : PATCH_HALO); ++hw)
+        for (int mw : {4, 8}) {
+            if (max_waves && mw != max_waves) continue;
+            int waves;
+            int64_t count;
+            if (!plan_batch_patches(b, mw, hw, grids, waves, count)) continue;
+            const double cost = patch_cost(f64, scheme == SCHEME_BKG, b->bnd, dev, count, waves, hw);
+            if (out.waves && cost >= out.cost) continue;
+            out.halo = hw;
+            out.waves = waves;
+            out.count = (int)count;
+            out.cost = cost;
+            best.swap(grids);
+        }
+    if (!out.waves) return LBFV_OK;
+    std::vector<PatchItem> items;
+    items.reserve(out.count);
+    for (int c = 0; c < (int)best.size(); ++c)
+        for (int py = 0; py < best[c].npy; ++py)
+            for (int px = 0; px < best[c].npx; ++px) items.push_back({c, px, py});
+    if (hipMalloc((void **)&out.d_grids, best.size() * sizeof(PatchGrid)) != hipSuccess ||
+        hipMalloc((void **)&out.d_items, items.size() * sizeof(PatchItem)) != hipSuccess) {
+        (void)hipGetLastError();
+        drop_patches(out);
+        return b->fail(LBFV_ENOMEM, "batch: cannot allocate the patch list");
+    }
+    if (hipMemcpy(out.d_grids, best.data(), best.size() * sizeof(PatchGrid), hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(out.d_items, items.data(), items.size() * sizeof(PatchItem), hipMemcpyHostToDevice) != hipSuccess) {
+        drop_patches(out);
+        return b->fail(LBFV_EHIP, "batch: patch list upload failed");
+    }
+    return LBFV_OK;
+}
+
+// Whether the patch form advances the batch: asked for by the autotuner, or by the sizes of the
+// meshes where no shape was set.  As for one case, a stream under capture gets marches.
+int batch_use_patches(lbfv_batch *b, int scheme, bool &yes) {
+    yes = false;
+    if (b->form == FORM_MARCH) return LBFV_OK;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(b->stream, &capture) != hipSuccess) (void)hipGetLastError();
+    else if (capture != hipStreamCaptureStatusNone) return LBFV_OK;
+    if (b->form == FORM_AUTO)
+        for (const auto &h : b->cases)
+            if ((int64_t)h.nx * h.ny > BATCH_PATCH_CELLS) return LBFV_OK;
+    if (!b->patches[scheme].halo) {
+        int st = make_patches(b, scheme, 0, 0);
+        if (st) return st;
+    }
+    yes = b->patches[scheme].waves > 0;
+    return LBFV_OK;
+}
+
+struct PatchArgs {
+    const void *params;
+    const PatchGrid *grids;
+    const PatchItem *items;
+    int parity, steps;
+    void *args[5];
+    PatchArgs(const lbfv_batch *b, int scheme, int parity_, int steps_)
+        : params(b->d_params), grids(b->patches[scheme].d_grids), items(b->patches[scheme].d_items), parity(parity_),
+          steps(steps_), args{&params, &grids, &items, &parity, &steps} {}
+    PatchArgs(const PatchArgs &) = delete;
+};
+unsigned patch_lds_bytes(const lbfv_batch *b, int scheme) {
+    return (unsigned)(PATCH_LDS * 64 * b->patches[scheme].waves * (is_f64(b->variant) ? 8 : 4));
+}
+
 struct BatchArgs {
     const void *params;
     const BatchItem *items;
@@ -2072,8 +2217,16 @@ int batch_launch_one(lbfv_batch *b, int scheme, int parity, bool two = false) {
     return LBFV_OK;
 }
 
-// a graph of gsteps launches of the current time block
-int batch_build_graph(lbfv_batch *b, int scheme, int parity0) {
+int batch_launch_patches(lbfv_batch *b, int scheme, int parity, int steps) {
+    PatchArgs a(b, scheme, parity, steps);
+    hipError_t e = hipLaunchKernel(batch_patch_fn_variant(b->variant, scheme, b->bnd), dim3(b->patches[scheme].count),
+                                   dim3(64 * b->patches[scheme].waves), a.args, patch_lds_bytes(b, scheme), b->stream);
+    if (e != hipSuccess) return b->fail(LBFV_EHIP, std::string("batch launch: ") + hipGetErrorString(e));
+    return LBFV_OK;
+}
+
+// a graph of gsteps launches of the current time block, or of the patch form
+int batch_build_graph(lbfv_batch *b, int scheme, int parity0, bool patch) {
     const bool two = b->tblock == 2;
     hipGraph_t g;
     if (hipGraphCreate(&g, 0) != hipSuccess) return b->fail(LBFV_EHIP, "hipGraphCreate failed");
@@ -2083,10 +2236,19 @@ int batch_build_graph(lbfv_batch *b, int scheme, int parity0) {
         a.bind();
         hipKernelNodeParams kp;
         memset(&kp, 0, sizeof(kp));
-        kp.func = batch_fn_variant(b->variant, scheme, b->bnd, two, batch_paired(b, two));
-        kp.gridDim = dim3(batch_grid(b, scheme, two));
-        kp.blockDim = dim3(batch_block(b, two));
-        kp.kernelParams = a.args;
+        PatchArgs pa(b, scheme, (parity0 + s) & 1, b->patches[scheme].halo);
+        if (patch) {
+            kp.func = batch_patch_fn_variant(b->variant, scheme, b->bnd);
+            kp.gridDim = dim3(b->patches[scheme].count);
+            kp.blockDim = dim3(64 * b->patches[scheme].waves);
+            kp.sharedMemBytes = patch_lds_bytes(b, scheme);
+            kp.kernelParams = pa.args;
+        } else {
+            kp.func = batch_fn_variant(b->variant, scheme, b->bnd, two, batch_paired(b, two));
+            kp.gridDim = dim3(batch_grid(b, scheme, two));
+            kp.blockDim = dim3(batch_block(b, two));
+            kp.kernelParams = a.args;
+        }
         hipGraphNode_t node;
         hipError_t e = hipGraphAddKernelNode(&node, g, prev ? &prev : nullptr, prev ? 1 : 0, &kp);
         if (e != hipSuccess) {
@@ -2095,10 +2257,30 @@ int batch_build_graph(lbfv_batch *b, int scheme, int parity0) {
         }
         prev = node;
     }
-    hipError_t e = hipGraphInstantiate(&b->gexec[scheme][parity0], g, nullptr, nullptr, 0);
+    hipError_t e = hipGraphInstantiate(&b->gexec[scheme + (patch ? 2 : 0)][parity0], g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (e != hipSuccess) return b->fail(LBFV_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
     return LBFV_OK;
+}
+
+// lbfv_batch_set_time_block, the form of the launches left as it is
+int batch_set_time_block(lbfv_batch *b, int32_t steps) {
+    if (steps == b->tblock) return LBFV_OK;
+    // launches in flight read the case table that is rewritten below
+    hipError_t es = hipStreamSynchronize(b->stream);
+    if (es != hipSuccess) return b->fail(LBFV_EHIP, std::string("batch: ") + hipGetErrorString(es));
+    // every case moves its current state into the other buffer in the new strip layout
+    const int w = steps == 2 ? STRIP2 : STRIP1;
+    for (auto &h : b->cases) {
+        hipError_t e = relayout(h, b->parity, w, b->stream);
+        if (e != hipSuccess) return b->fail(LBFV_EHIP, std::string("batch relayout: ") + hipGetErrorString(e));
+        h.set_strip(w);
+    }
+    b->parity ^= 1;
+    b->tblock = steps;
+    int st = is_f64(b->variant) ? batch_upload_params<double>(b) : batch_upload_params<float>(b);
+    if (!st) st = batch_build_items(b);
+    return st;
 }
 
 template <typename T, typename S>
@@ -2205,6 +2387,7 @@ int lbfv_batch_destroy(lbfv_batch *b) {
     for (auto &h : b->cases) free_case(h);
     if (b->d_params) (void)hipFree(b->d_params);
     if (b->d_items) (void)hipFree(b->d_items);
+    for (auto &p : b->patches) drop_patches(p);
     delete b;
     return LBFV_OK;
 }
@@ -2214,6 +2397,7 @@ int lbfv_batch_set_shape(lbfv_batch *b, int32_t graph_steps, int32_t rows) {
     if (graph_steps < 0 || rows < 0) return b->fail(LBFV_EINVAL, "bad shape");
     if (graph_steps > 0) b->gsteps = graph_steps;
     batch_drop_graphs(b);
+    if (rows > 0) b->form = FORM_MARCH;
     if (rows > 0 && rows != b->rows) {
         b->rows = rows;
         return batch_build_items(b);
@@ -2231,6 +2415,7 @@ int lbfv_batch_get_shape(const lbfv_batch *b, int32_t *graph_steps, int32_t *row
 int lbfv_batch_set_grid_form(lbfv_batch *b, int32_t wave_per_item) {
     if (!b) return LBFV_EINVAL;
     if (wave_per_item != 0 && wave_per_item != 1) return b->fail(LBFV_EINVAL, "lbfv_batch_set_grid_form: 0 or 1");
+    b->form = FORM_MARCH;
     if ((bool)wave_per_item != b->wave_per_item) {
         b->wave_per_item = wave_per_item;
         batch_drop_graphs(b);
@@ -2247,6 +2432,7 @@ int lbfv_batch_get_grid_form(const lbfv_batch *b, int32_t *wave_per_item) {
 int lbfv_batch_set_wave_pairs(lbfv_batch *b, int32_t on) {
     if (!b) return LBFV_EINVAL;
     if (on != 0 && on != 1) return b->fail(LBFV_EINVAL, "lbfv_batch_set_wave_pairs: 0 or 1");
+    b->form = FORM_MARCH;
     if ((bool)on != b->pairs) {
         b->pairs = on;
         batch_drop_graphs(b);
@@ -2263,22 +2449,8 @@ int lbfv_batch_get_wave_pairs(const lbfv_batch *b, int32_t *on) {
 int lbfv_batch_set_time_block(lbfv_batch *b, int32_t steps) {
     if (!b) return LBFV_EINVAL;
     if (steps != 1 && steps != 2) return b->fail(LBFV_EINVAL, "lbfv_batch_set_time_block: steps must be 1 or 2");
-    if (steps == b->tblock) return LBFV_OK;
-    // launches in flight read the case table that is rewritten below
-    hipError_t es = hipStreamSynchronize(b->stream);
-    if (es != hipSuccess) return b->fail(LBFV_EHIP, std::string("batch: ") + hipGetErrorString(es));
-    // every case moves its current state into the other buffer in the new strip layout
-    const int w = steps == 2 ? STRIP2 : STRIP1;
-    for (auto &h : b->cases) {
-        hipError_t e = relayout(h, b->parity, w, b->stream);
-        if (e != hipSuccess) return b->fail(LBFV_EHIP, std::string("batch relayout: ") + hipGetErrorString(e));
-        h.set_strip(w);
-    }
-    b->parity ^= 1;
-    b->tblock = steps;
-    int st = is_f64(b->variant) ? batch_upload_params<double>(b) : batch_upload_params<float>(b);
-    if (!st) st = batch_build_items(b);
-    return st;
+    b->form = FORM_MARCH;
+    return batch_set_time_block(b, steps);
 }
 
 int lbfv_batch_get_time_block(const lbfv_batch *b, int32_t *steps) {
@@ -2299,8 +2471,12 @@ int lbfv_batch_autotune(lbfv_batch *b, int scheme, int32_t trial_steps, double *
         (void)hipGetLastError();
         return b->fail(LBFV_ENOMEM, "batch autotune: cannot allocate the state copy");
     }
-    const int parity0 = b->parity, rows0 = b->rows, gsteps0 = b->gsteps, tb0 = b->tblock;
+    const int parity0 = b->parity, rows0 = b->rows, gsteps0 = b->gsteps, tb0 = b->tblock, form0 = b->form;
     const bool wpi0 = b->wave_per_item, pairs0 = b->pairs;
+    int one_rows = rows0;                    // the fastest marches of one step per launch
+    bool one_wpi = wpi0;
+    double best_one = INFINITY;
+    int patch_halo = 0, patch_waves = 0;     // the patch form, where it is fastest
     hipError_t e = hipSuccess;
     size_t off = 0;
     for (const auto &h : b->cases) {
@@ -2321,11 +2497,27 @@ int lbfv_batch_autotune(lbfv_batch *b, int scheme, int32_t trial_steps, double *
     bool best_wpi = wpi0, best_pairs = pairs0;
     double best = INFINITY;
     b->gsteps = ts;
+    b->form = FORM_MARCH;
+    // one replay of a graph of ts launches of `per` steps after a first that builds and warms it:
+    // ms per step
+    auto replay = [&](int per, double &ms) {
+        int rs = lbfv_batch_step(b, scheme, per * ts);
+        if (rs) return rs;
+        float t = 0;
+        hipError_t he = hipEventRecord(e0, b->stream);
+        if (he == hipSuccess && (rs = lbfv_batch_step(b, scheme, per * ts))) return rs;
+        if (he == hipSuccess) he = hipEventRecord(e1, b->stream);
+        if (he == hipSuccess) he = hipEventSynchronize(e1);
+        if (he == hipSuccess) he = hipEventElapsedTime(&t, e0, e1);
+        if (he != hipSuccess) return b->fail(LBFV_EHIP, std::string("batch autotune timing: ") + hipGetErrorString(he));
+        ms = t / (per * ts);
+        return (int)LBFV_OK;
+    };
     // (time block, pair of waves per item): one step; two steps with one wave or a pair
     for (auto form : std::vector<std::pair<int, bool>>{{1, false}, {2, false}, {2, true}}) {
         const int tb = form.first;
         b->pairs = form.second;
-        if (st || (st = lbfv_batch_set_time_block(b, tb))) break;
+        if (st || (st = batch_set_time_block(b, tb))) break;
         std::vector<int> heights = {2, 4, 8, 16, 32, 64};
         for (int r : batch_balanced_rows(b, batch_slots(b, scheme, tb == 2), 3))
             if (std::find(heights.begin(), heights.end(), r) == heights.end()) heights.push_back(r);
@@ -2334,25 +2526,46 @@ int lbfv_batch_autotune(lbfv_batch *b, int scheme, int32_t trial_steps, double *
             b->wave_per_item = trial & 1;
             b->rows = r;
             if ((st = batch_build_items(b))) break;
-            if ((st = lbfv_batch_step(b, scheme, tb * ts))) break;
-            float t = 0;
-            e = hipEventRecord(e0, b->stream);
-            if (e == hipSuccess && (st = lbfv_batch_step(b, scheme, tb * ts))) break;
-            if (e == hipSuccess) e = hipEventRecord(e1, b->stream);
-            if (e == hipSuccess) e = hipEventSynchronize(e1);
-            if (e == hipSuccess) e = hipEventElapsedTime(&t, e0, e1);
-            if (e != hipSuccess) {
-                st = b->fail(LBFV_EHIP, std::string("batch autotune timing: ") + hipGetErrorString(e));
-                break;
-            }
-            if (t / (tb * ts) < best) {
-                best = t / (tb * ts);
+            double ms;
+            if ((st = replay(tb, ms))) break;
+            if (ms < best) {
+                best = ms;
                 best_rows = r;
                 best_tb = tb;
                 best_wpi = b->wave_per_item;
                 best_pairs = b->pairs;
             }
+            if (tb == 1 && ms < best_one) {
+                best_one = ms;
+                one_rows = r;
+                one_wpi = b->wave_per_item;
+            }
         }
+    }
+    // the patch form at each halo width and workgroup size that the cost model does not put far
+    // behind the fastest marches
+    if (!st && !(st = batch_set_time_block(b, 1))) {
+        b->form = FORM_PATCH;
+        for (int k = 0; k < 2 * PATCH_HALO && !st; ++k) {
+            const int hw = 1 + k / 2, mw = k & 1 ? 8 : 4;
+            if ((st = make_patches(b, scheme, hw, mw))) break;
+            if (!b->patches[scheme].waves || b->patches[scheme].cost > 1.5e3 * best) continue;
+            batch_drop_graphs(b);
+            double ms;
+            if ((st = replay(hw, ms))) break;
+            if (ms < best) {
+                best = ms;
+                patch_halo = hw;
+                patch_waves = mw;
+            }
+        }
+    }
+    if (patch_halo) {
+        // the march controls then hold the fastest march of the same (one-step) layout
+        best_tb = 1;
+        best_pairs = false;
+        best_rows = one_rows;
+        best_wpi = one_wpi;
     }
     // restore the layout, the state, the parity and the graph length (the saved state is
     // in the layout of the entry time block); keep the fastest shape
@@ -2377,10 +2590,17 @@ int lbfv_batch_autotune(lbfv_batch *b, int scheme, int32_t trial_steps, double *
     (void)hipFree(save);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
+    drop_patches(b->patches[scheme]);
+    b->form = st ? form0 : FORM_MARCH;
     if (st) return st;
     if (st2) return st2;
     if (re != hipSuccess) return b->fail(LBFV_EHIP, std::string("batch autotune restore: ") + hipGetErrorString(re));
-    if ((st = lbfv_batch_set_time_block(b, best_tb))) return st;
+    if ((st = batch_set_time_block(b, best_tb))) return st;
+    if (patch_halo) {
+        if ((st = make_patches(b, scheme, patch_halo, patch_waves))) return st;
+        b->form = FORM_PATCH;
+    }
+    batch_drop_graphs(b);
     if (best_ms) *best_ms = best;
     return LBFV_OK;
 }
@@ -2514,14 +2734,17 @@ int lbfv_batch_step(lbfv_batch *b, int scheme, int32_t n) {
     if (!b) return LBFV_EINVAL;
     if (scheme != LBFV_DUGKS && scheme != LBFV_BKG) return b->fail(LBFV_EINVAL, "unknown scheme");
     if (n < 0) return b->fail(LBFV_EINVAL, "nsteps must be >= 0");
+    bool patch = false;
+    int st = batch_use_patches(b, scheme, patch);
+    if (st) return st;
     // with a time block of 2 every launch advances two steps; an odd last step is a
-    // one-step launch on the same layout
+    // one-step launch on the same layout.  The patch form takes up to its halo width.
     const bool two = b->tblock == 2;
-    const int per = two ? 2 : 1;
+    const int per = patch ? b->patches[scheme].halo : (two ? 2 : 1);
     while (n >= per * b->gsteps) {
-        hipGraphExec_t &g = b->gexec[scheme][b->parity];
+        hipGraphExec_t &g = b->gexec[scheme + (patch ? 2 : 0)][b->parity];
         if (!g) {
-            int st = batch_build_graph(b, scheme, b->parity);
+            st = batch_build_graph(b, scheme, b->parity, patch);
             if (st) return st;
         }
         hipError_t e = hipGraphLaunch(g, b->stream);
@@ -2529,15 +2752,12 @@ int lbfv_batch_step(lbfv_batch *b, int scheme, int32_t n) {
         b->parity ^= (b->gsteps & 1);
         n -= per * b->gsteps;
     }
-    for (; n >= per; n -= per) {
-        int st = batch_launch_one(b, scheme, b->parity, two);
+    while (n > 0) {
+        const int k = std::min(n, per);
+        st = patch ? batch_launch_patches(b, scheme, b->parity, k) : batch_launch_one(b, scheme, b->parity, k == 2);
         if (st) return st;
         b->parity ^= 1;
-    }
-    if (n > 0) {
-        int st = batch_launch_one(b, scheme, b->parity);
-        if (st) return st;
-        b->parity ^= 1;
+        n -= k;
     }
     return LBFV_OK;
 }

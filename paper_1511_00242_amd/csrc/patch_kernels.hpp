@@ -24,7 +24,9 @@
 namespace lbfv {
 
 constexpr int PATCH_WAVES = 8;    // most waves of a workgroup: 512 lanes, two waves per SIMD
-constexpr int PATCH_LDS = 15;     // values per lane in LDS: phi (9) and the north face (6)
+// Values per lane in LDS: phi (9) and the north face (6), side by side, so that they are reached
+// by constant offsets from one address; an odd count, so that lanes in a row meet no bank conflict.
+constexpr int PATCH_LDS = 15;
 
 // Patches of one mesh: an axis of n cells split into np runs of qn or qn + 1 cells, the rn
 // longer ones first.
@@ -40,22 +42,26 @@ template <typename T, typename S, int SCHEME, bool BND, bool REF>
 struct Patch : March<T, S, SCHEME, BND, 2, REF> {
     using M = March<T, S, SCHEME, BND, 2, REF>;
     using M::P;
-    using M::col;
     using M::lane;
-    int row;                    // this lane's row (col: its column), outside the mesh in halo and ghost cells
-    int colE, rowN;             // ... counted from the east and the north ghost cells
-    uint32_t off;               // byte offset of its cell within a direction plane
+    uint32_t off;               // byte offset of this lane's cell within a direction plane
     bool out;                   // the lane's result is stored
     int slot, up, down;         // LDS slots of its cell and of the cells above and below
     T lamN, bnN, isy, cdy;      // metrics of its north face and row
-    // Sides inside the patch (-1: none), the same for the workgroup, and what the lanes at them
-    // need at every step, kept in registers: read from the parameters inside the loop, each
-    // value is a scalar load that a lone wave waits for (twice the time of a step).
-    int kW, kE, kS, kN;
-    bool wS, wN;                // a wall segment on the south / north side
-    bool fixed;                 // this lane's ghost cell holds a constant state (inflow), kept in LDS
-    bool ruleS, ruleN;          // the ghost cell below / above this lane's cell follows from its rows
-    bool rowG;                  // this lane is that ghost cell on the south side
+    // What the patch's sides ask for (`sides`, the same for the workgroup) and this lane's part in
+    // it (`part`), one bit each: as separate flags they fill the scalar registers and push the
+    // equilibrium's constants into vector registers (188 for FP64 DUGKS, two waves per SIMD).
+    // The side's values stay in registers too: read from the parameters inside the step loop,
+    // each is a scalar load that a lone wave waits for (twice the time of a step).
+    uint32_t sides, part;
+    enum : uint32_t { EXT_W = 1, MIR_W = 2, WALL_W = 4, EXT_E = 8, MIR_E = 16, WALL_E = 32,   // sides
+                      SOUTH = 64, MIR_S = 128, WALL_S = 256, NORTH = 512, MIR_N = 1024, WALL_N = 2048 };
+    enum : uint32_t { GHOST_W = 1, FACE_W = 2, GHOST_E = 4,   // column -1, column 0, column nx
+                      FIXED = 8,        // a ghost cell that holds a constant state (inflow), kept in LDS
+                      ROW_G = 16,       // a south ghost cell that follows from its rows
+                      NEXT_S = 32, NEXT_N = 64,   // the cell next to such a ghost cell
+                      MIRROR = 128,     // ... which is mirrored (symmetry), not extrapolated
+                      LAST = 256, FIRST = 512,    // its north face is the north / south side's
+                      BOUNCE = 1024, REFLECT = 2048 };   // ... and a wall / a symmetry plane there
     T ex, ey;                   // its ghost factors, beyond an x side and beyond a y side
     T bx[2], by[2];             // wall terms of its x-face and its y-face
 
@@ -71,14 +77,11 @@ struct Patch : March<T, S, SCHEME, BND, 2, REF> {
         // lanes past the last whole row of the wave repeat its last lane (and store nothing)
         const int l = min(lane, G.fit * G.tw - 1);
         const int seg = l / G.tw, c = l - seg * G.tw;
-        col = c0 + c;
-        row = r0 + wave * G.fit + seg;
-        colE = col - nx;
-        rowN = row - ny;
+        const int col = c0 + c, row = r0 + wave * G.fit + seg;
         out = lane == l && col >= ox0 && col < ox1 && row >= oy0 && row < oy1;
         slot = wave * 64 + lane;
-        up = lane == l ? above(G, waves, wave, seg, c) : slot;
-        down = lane == l ? below(G, wave, seg, c) : slot;
+        up = lane == l ? slot_above(G, waves, wave, seg, c) : slot;
+        down = lane == l ? slot_below(G, wave, seg, c) : slot;
 
         // a periodic axis wraps once; what is still outside belongs to lanes past the halo
         int cc = col, rr = row;
@@ -110,31 +113,38 @@ struct Patch : March<T, S, SCHEME, BND, 2, REF> {
         isy = P.ym[2 * (ny + 1) + rr];
         cdy = P.ym[3 * ny + 2 + rr];
         if (BND) {
-            // a patch whose halo reaches beyond a side holds the side's ghost cells
-            kW = !this->per_x && ox0 < G.halo ? P.bc[SIDE_W] : -1;
-            kE = !this->per_x && ox1 + G.halo > nx ? P.bc[SIDE_E] : -1;
-            kS = !this->per_y && oy0 < G.halo ? P.bc[SIDE_S] : -1;
-            kN = !this->per_y && oy1 + G.halo > ny ? P.bc[SIDE_N] : -1;
-            wS = kS >= 0 && P.wfrom[SIDE_S] >= 0;
-            wN = kN >= 0 && P.wfrom[SIDE_N] >= 0;
-            this->segS = wS && col >= P.wfrom[SIDE_S];
-            this->segN = wN && col >= P.wfrom[SIDE_N];
-            const int sx = col <= 0 ? SIDE_W : SIDE_E, sy = row <= 0 ? SIDE_S : SIDE_N;
-            const bool seg_y = row <= 0 ? this->segS : this->segN;
+            // a patch whose halo reaches beyond a side holds the side's ghost cells (kind -1: none)
+            const int kW = !this->per_x && ox0 < G.halo ? P.bc[SIDE_W] : -1;
+            const int kE = !this->per_x && ox1 + G.halo > nx ? P.bc[SIDE_E] : -1;
+            const int kS = !this->per_y && oy0 < G.halo ? P.bc[SIDE_S] : -1;
+            const int kN = !this->per_y && oy1 + G.halo > ny ? P.bc[SIDE_N] : -1;
+            const int fromS = kS >= 0 ? P.wfrom[SIDE_S] : -1, fromN = kN >= 0 ? P.wfrom[SIDE_N] : -1;
+            auto ext = [](int k) { return k == BC_WALL || k == BC_OUTFLOW; };
+            sides = (ext(kW) ? EXT_W : 0) | (kW == BC_SYMMETRY ? MIR_W : 0) | (kW == BC_WALL ? WALL_W : 0) |
+                    (ext(kE) ? EXT_E : 0) | (kE == BC_SYMMETRY ? MIR_E : 0) | (kE == BC_WALL ? WALL_E : 0) |
+                    (kS >= 0 ? SOUTH : 0) | (kS == BC_SYMMETRY ? MIR_S : 0) | (kS == BC_WALL || fromS >= 0 ? WALL_S : 0) |
+                    (kN >= 0 ? NORTH : 0) | (kN == BC_SYMMETRY ? MIR_N : 0) | (kN == BC_WALL || fromN >= 0 ? WALL_N : 0);
+            const bool segS = fromS >= 0 && col >= fromS, segN = fromN >= 0 && col >= fromN;
+            const bool southern = row <= 0, seg_y = southern ? segS : segN;
+            const int sx = col <= 0 ? SIDE_W : SIDE_E, sy = southern ? SIDE_S : SIDE_N, ky = southern ? kS : kN;
             const bool beyond_x = (kW >= 0 && col == -1) || (kE >= 0 && col == nx);
             const bool beyond_y = (kS >= 0 && row == -1) || (kN >= 0 && row == ny);
             // (the y side's rule holds in the corners)
-            const int side = beyond_y ? sy : sx;
-            fixed = (beyond_y && !seg_y && (row == -1 ? kS : kN) == BC_INFLOW) ||
-                    (!beyond_y && beyond_x && (col == -1 ? kW : kE) == BC_INFLOW);
-            const bool row_rule = seg_y || (row <= 0 ? kS : kN) != BC_INFLOW;
-            ruleS = kS >= 0 && row == 0 && row_rule;
-            rowG = kS >= 0 && row == -1 && row_rule && lane == l;
-            ruleN = kN >= 0 && rowN == -1 && row_rule;
-            if (rowG) down = above(G, waves, up >> 6, ((up & 63) - c) / G.tw, c);   // its second row: row 1
+            const bool fixed = beyond_y ? ky == BC_INFLOW && !seg_y : beyond_x && (col == -1 ? kW : kE) == BC_INFLOW;
+            const bool rule = ky >= 0 && (seg_y || ky != BC_INFLOW);   // ghost rows that follow from their rows
+            const bool first = kS >= 0 && row == -1, last = kN >= 0 && row == ny - 1;
+            part = (col == -1 ? GHOST_W : 0) | (col == 0 ? FACE_W : 0) | (col == nx ? GHOST_E : 0) | (fixed ? FIXED : 0) |
+                   (first && rule && lane == l ? ROW_G : 0) | (rule && row == 0 && kS >= 0 ? NEXT_S : 0) |
+                   (last && kN >= 0 && (segN || kN != BC_INFLOW) ? NEXT_N : 0) | (last ? LAST : 0) | (first ? FIRST : 0);
+            // a one-row mesh has no rule of its own here: ny >= 2, so row 0 is not row ny - 1
+            if (ky == BC_SYMMETRY && !seg_y) part |= MIRROR;
+            if ((first || last) && (ky == BC_WALL || seg_y)) part |= BOUNCE;
+            if ((first || last) && ky == BC_SYMMETRY && !seg_y) part |= REFLECT;
+            if (part & ROW_G) down = slot_above(G, waves, up >> 6, ((up & 63) - c) / G.tw, c);   // its second row: row 1
             if (fixed) {
+                const int side = beyond_y ? sy : sx;
 #pragma unroll
-                for (int a = 0; a < 9; ++a) lds[a * (64 * waves) + slot] = P.gin[side][a];
+                for (int a = 0; a < 9; ++a) lds[slot * PATCH_LDS + a] = P.gin[side][a];
             }
             ex = P.gext[sx];
             ey = seg_y ? P.ext[sy] : P.gext[sy];
@@ -144,13 +154,20 @@ struct Patch : March<T, S, SCHEME, BND, 2, REF> {
             by[1] = seg_y ? P.wsv[sy][1] : P.bcv[sy][1];
         }
     }
-    __device__ __forceinline__ int above(const PatchGrid &G, int waves, int wave, int seg, int c) const {
+    __device__ __forceinline__ int slot_above(const PatchGrid &G, int waves, int wave, int seg, int c) const {
         return seg + 1 < G.fit ? wave * 64 + (seg + 1) * G.tw + c
                                : (wave + 1 < waves ? (wave + 1) * 64 + c : wave * 64 + seg * G.tw + c);
     }
-    __device__ __forceinline__ int below(const PatchGrid &G, int wave, int seg, int c) const {
+    __device__ __forceinline__ int slot_below(const PatchGrid &G, int wave, int seg, int c) const {
         return seg > 0 ? wave * 64 + (seg - 1) * G.tw + c
                        : (wave > 0 ? (wave - 1) * 64 + (G.fit - 1) * G.tw + c : wave * 64 + c);
+    }
+
+    // A value whose use stays where it is written: the compiler otherwise forms the wall terms of
+    // all directions before the loop and holds 16 registers for them.
+    static __device__ __forceinline__ T here(T v) {
+        asm volatile("" : "+v"(v));
+        return v;
     }
 
     // the march's yface with this lane's own metrics
@@ -169,51 +186,56 @@ struct Patch : March<T, S, SCHEME, BND, 2, REF> {
     // The ghost columns of a row (x sides first, as in the march; inflow states stay in LDS): the
     // march's ghost rule, one branch per kind of side.
     __device__ __forceinline__ void ghost_columns(T (&phi)[9]) const {
-        if (kW == BC_SYMMETRY) {
+        const bool w = part & GHOST_W, e = part & GHOST_E;
+        if (sides & MIR_W) {
 #pragma unroll
             for (int a = 0; a < 9; ++a) {
                 const T m = shl1(phi[MIRX[a]]);
-                phi[a] = col == -1 ? m : phi[a];
+                phi[a] = w ? m : phi[a];
             }
-        } else if (kW >= 0 && kW != BC_INFLOW) {
+        }
+        if (sides & EXT_W) {
 #pragma unroll
             for (int a = 0; a < 9; ++a) {
                 const T g1 = shl1(phi[a]), g2 = shl1(g1);
                 const T v = fma(g1 - g2, ex, g1);
-                phi[a] = col == -1 ? v : phi[a];
+                phi[a] = w ? v : phi[a];
             }
         }
-        if (kE == BC_SYMMETRY) {
+        if (sides & MIR_E) {
 #pragma unroll
             for (int a = 0; a < 9; ++a) {
                 const T m = shr1(phi[MIRX[a]]);
-                phi[a] = colE == 0 ? m : phi[a];
+                phi[a] = e ? m : phi[a];
             }
-        } else if (kE >= 0 && kE != BC_INFLOW) {
+        }
+        if (sides & EXT_E) {
 #pragma unroll
             for (int a = 0; a < 9; ++a) {
                 const T g1 = shr1(phi[a]), g2 = shr1(g1);
                 const T v = fma(g1 - g2, ex, g1);
-                phi[a] = colE == 0 ? v : phi[a];
+                phi[a] = e ? v : phi[a];
             }
         }
     }
 
     // the ghost rule beyond a y side from the adjacent row r1 and the next one r2
-    __device__ __forceinline__ void ghost_of(int kind, bool wall, const T (&r1)[9], const T (&r2)[9], T (&out)[9]) const {
+    __device__ __forceinline__ void ghost_of(const T (&r1)[9], const T (&r2)[9], T (&out)[9]) const {
+        const bool mirror = part & MIRROR;
 #pragma unroll
         for (int a = 0; a < 9; ++a) {
             const T v = fma(r1[a] - r2[a], ey, r1[a]);
-            out[a] = kind == BC_SYMMETRY && !wall ? r1[MIRY[a]] : v;
+            out[a] = mirror ? r1[MIRY[a]] : v;
         }
     }
 
     // `steps` (at most G.halo) time steps of patch (px, py); lds holds PATCH_LDS values per lane
     __device__ __forceinline__ void run(const PatchGrid &G, int px, int py, int steps, T *lds) {
-        const int waves = (int)(blockDim.x >> 6), n = (int)blockDim.x;
+        const int waves = (int)(blockDim.x >> 6);
         const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
         place(G, px, py, wave, waves, lds);
-        T *face = lds + 9 * n;
+        T *const mine = lds + slot * PATCH_LDS;
+        const T *const above = lds + up * PATCH_LDS, *const below = lds + down * PATCH_LDS;
         const int bytes = (int)(P.plane * (int64_t)sizeof(S));
         T x[9];
 #pragma unroll
@@ -226,27 +248,27 @@ struct Patch : March<T, S, SCHEME, BND, 2, REF> {
             T phi[9], psi[9];
             this->cell_t(x, phi, psi);
             if constexpr (BND) ghost_columns(phi);
-            if (!BND || !fixed) {
+            if (!BND || !(part & FIXED)) {
 #pragma unroll
-                for (int a = 0; a < 9; ++a) lds[a * n + slot] = phi[a];
+                for (int a = 0; a < 9; ++a) mine[a] = phi[a];
             }
             __syncthreads();
             T hi[9], lo[9];
 #pragma unroll
             for (int a = 0; a < 9; ++a) {
-                hi[a] = lds[a * n + up];
-                lo[a] = BND || EY[a] != 0 ? lds[a * n + down] : (T)0;
+                hi[a] = above[a];
+                lo[a] = BND || EY[a] != 0 ? below[a] : (T)0;
             }
-            if (BND && fixed) {
+            if (BND && (part & FIXED)) {
 #pragma unroll
-                for (int a = 0; a < 9; ++a) phi[a] = lds[a * n + slot];
+                for (int a = 0; a < 9; ++a) phi[a] = mine[a];
             }
-            if (BND && kS >= 0) {
-                if (rowG) ghost_of(kS, this->segS, hi, lo, phi);   // (lo holds row 1 there)
-                if (ruleS) ghost_of(kS, this->segS, phi, hi, lo);
+            if (BND && (sides & SOUTH)) {
+                if (part & ROW_G) ghost_of(hi, lo, phi);   // (lo holds row 1 there)
+                if (part & NEXT_S) ghost_of(phi, hi, lo);
             }
-            if (BND && kN >= 0) {
-                if (ruleN) ghost_of(kN, this->segN, phi, lo, hi);
+            if (BND && (sides & NORTH)) {
+                if (part & NEXT_N) ghost_of(phi, lo, hi);
             }
             T dy[9];
 #pragma unroll
@@ -254,28 +276,23 @@ struct Patch : March<T, S, SCHEME, BND, 2, REF> {
             // the north face first: its values are what the row above waits for
             T fN[9];
             north_face(phi, hi, fN);
-            if (BND && kN >= 0) {
-                const bool last = rowN == -1;
-                if (kN == BC_WALL || wN) this->template bounce<0, 1>(fN, by[0], by[1], last && (kN == BC_WALL || this->segN));
-                if (kN == BC_SYMMETRY) this->template specular<0, 1>(fN, last && !this->segN);
-            }
-            if (BND && kS >= 0) {
-                const bool first = row == -1;   // the ghost row's north face is the south face of row 0
-                if (kS == BC_WALL || wS) this->template bounce<0, -1>(fN, by[0], by[1], first && (kS == BC_WALL || this->segS));
-                if (kS == BC_SYMMETRY) this->template specular<0, -1>(fN, first && !this->segS);
-            }
+            // (a south ghost cell's north face is the south face of row 0)
+            if (BND && (sides & WALL_N)) this->template bounce<0, 1>(fN, here(by[0]), here(by[1]), (part & (LAST | BOUNCE)) == (LAST | BOUNCE));
+            if (BND && (sides & MIR_N)) this->template specular<0, 1>(fN, (part & (LAST | REFLECT)) == (LAST | REFLECT));
+            if (BND && (sides & WALL_S)) this->template bounce<0, -1>(fN, here(by[0]), here(by[1]), (part & (FIRST | BOUNCE)) == (FIRST | BOUNCE));
+            if (BND && (sides & MIR_S)) this->template specular<0, -1>(fN, (part & (FIRST | REFLECT)) == (FIRST | REFLECT));
             this->template face_mix<1>(fN);
             int q = 0;
 #pragma unroll
             for (int a = 0; a < 9; ++a)
-                if (EY[a] != 0) face[q++ * n + slot] = fN[a];
+                if (EY[a] != 0) mine[9 + q++] = fN[a];
             // x-faces while the row below writes
             T fW[9];
             this->xface(phi, dy, isy, fW);
-            if (BND && kW == BC_WALL) this->template bounce<-1, 0>(fW, bx[0], bx[1], col == 0);
-            if (BND && kW == BC_SYMMETRY) this->template specular<-1, 0>(fW, col == 0);
-            if (BND && kE == BC_WALL) this->template bounce<1, 0>(fW, bx[0], bx[1], colE == 0);
-            if (BND && kE == BC_SYMMETRY) this->template specular<1, 0>(fW, colE == 0);
+            if (BND && (sides & WALL_W)) this->template bounce<-1, 0>(fW, here(bx[0]), here(bx[1]), part & FACE_W);
+            if (BND && (sides & MIR_W)) this->template specular<-1, 0>(fW, part & FACE_W);
+            if (BND && (sides & WALL_E)) this->template bounce<1, 0>(fW, here(bx[0]), here(bx[1]), part & GHOST_E);
+            if (BND && (sides & MIR_E)) this->template specular<1, 0>(fW, part & GHOST_E);
             this->template face_mix<0>(fW);
             __syncthreads();
             q = 0;
@@ -287,7 +304,7 @@ struct Patch : March<T, S, SCHEME, BND, 2, REF> {
                     u = fma(EX[a] > 0 ? -this->cdx : this->cdx, fE - fW[a], u);
                 }
                 if (EY[a] != 0) {
-                    const T fS = face[q++ * n + down];
+                    const T fS = below[9 + q++];
                     u = fma(EY[a] > 0 ? -cdy : cdy, fN[a] - fS, u);
                 }
                 // what a one-step launch would store and read back
@@ -325,6 +342,24 @@ __global__ __launch_bounds__(64 * PATCH_WAVES) void patch_ptr_kernel(const StepP
     const int py = b / G.npx, px = b - py * G.npx;
     Patch<T, S, SCHEME, true, REF> m(P, (const S *)P.buf[parity], (S *)P.buf[parity ^ 1]);
     m.run(G, px, py, steps, (T *)patch_lds);
+}
+
+// The batched form: one workgroup per patch of any case; each case has its own mesh and patches,
+// all patches the same waves and at most the same steps.
+struct PatchItem {
+    int32_t c, px, py;
+};
+template <typename T, typename S, int SCHEME, bool BND>
+__global__ __launch_bounds__(64 * PATCH_WAVES) void batch_patch_kernel(const StepParams<T> *__restrict__ cases,
+                                                                       const PatchGrid *__restrict__ grids,
+                                                                       const PatchItem *__restrict__ items, int parity,
+                                                                       int steps) {
+    extern __shared__ char patch_lds[];
+    const PatchItem it = items[xcd_block()];
+    const StepParams<T> &P = cases[it.c];
+    const PatchGrid G = grids[it.c];
+    Patch<T, S, SCHEME, BND, false> m(P, (const S *)P.buf[parity], (S *)P.buf[parity ^ 1]);
+    m.run(G, it.px, it.py, steps, (T *)patch_lds);
 }
 
 }  // namespace lbfv

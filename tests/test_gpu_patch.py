@@ -16,6 +16,15 @@ from test_gpu_parity import ALL_SCHEMES, _mixed_workload, _periodic_workload, _s
 
 pytestmark = pytest.mark.gpu
 
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need an MI355X"
+    torch.cuda.set_device(0)
+    yield
+
+
 FORMS = {"f64": (L.LBFV_FP64, L.LBFV_STORE_NATIVE), "f32": (L.LBFV_FP32, L.LBFV_STORE_DEV_FP32),
          "bf16": (L.LBFV_FP32, L.LBFV_STORE_DEV_BF16), "f16": (L.LBFV_FP32, L.LBFV_STORE_DEV_FP16)}
 
@@ -127,3 +136,34 @@ def test_captured_steps_replay():
         ctx.set_tile(4, 1)
         ctx.dugks_step(2 + 12)
         assert np.array_equal(ctx.get_f(), f)
+
+
+@pytest.mark.parametrize("form", sorted(FORMS))
+def test_batch_patches_equal_one_step_marches(form):
+    """The batched patch form on uneven meshes and sides, in a batch with and without
+    non-periodic sides, through graph replays and leftover steps; and after the autotuner."""
+    compute, storage = FORMS[form]
+    sided = [w for nx, ny in ((9, 8), (33, 64), (70, 21)) for w in workloads(nx, ny)
+             if not any(isinstance(b, tuple) and b[0] == "wall_from" for b in w.bcs)]
+    for cases in (sided, [_periodic_workload(nx, ny, 3) for nx, ny in ((9, 9), (64, 10), (130, 37))]):
+        for scheme in (L.LBFV_DUGKS, L.LBFV_BKG):
+            outs = []
+            for how in ("march", "patch", "tuned"):
+                b = L.Batch(cases, compute=compute, storage=storage)
+                for i, w in enumerate(cases):
+                    b.init_equilibrium(i, w.rho, w.ux, w.uy)
+                b.set_shape(graph_steps=3)
+                if how == "march":
+                    b.set_shape(rows=5)
+                elif how == "tuned":
+                    b.autotune(scheme, 4)
+                    if storage in (L.LBFV_STORE_DEV_BF16, L.LBFV_STORE_DEV_FP16) and b.get_time_block() == 2:
+                        b.close()   # two steps between roundings: other values by design
+                        continue
+                for n in (1, 29, 6):
+                    b.step(scheme, n)
+                outs.append([b.get_f(i) for i in range(len(cases))])
+                b.close()
+            for other in outs[1:]:
+                for w, f, g in zip(cases, outs[0], other):
+                    assert np.all(np.isfinite(f)) and np.array_equal(f, g), w.name
