@@ -193,9 +193,11 @@ int lbfv_totals_device(lbfv_ctx *ctx, double *dev_out);
  * A context on which no shape has been set (by this call, lbfv_set_wave_pairs,
  * lbfv_set_time_block or lbfv_autotune) advances a small mesh (at most 2^20 cells) in the
  * patch form instead: rectangular patches with one cell per lane, up to 8 steps per launch,
- * each patch recomputing a halo.  The results are those of one-step launches bit for bit, in
- * every storage (16-bit storage is rounded after every step); checks fall due exactly at
- * check_every.  A stream under capture always gets marches, one launch per time block. */
+ * each patch recomputing a halo, and in FP64 and FP32 a larger one with four (doubly
+ * periodic) or two steps per launch.  The results are those of one-step launches bit for bit,
+ * in every storage (16-bit storage is rounded after every step); checks fall due exactly at
+ * check_every, and the state ends each call in the buffer that one-step launches would leave
+ * it in.  A stream under capture gets one-step launches. */
 int lbfv_set_tile(lbfv_ctx *ctx, int32_t rows, int32_t waves_per_block);
 int lbfv_get_tile(const lbfv_ctx *ctx, int32_t *rows, int32_t *waves_per_block);
 /* Work split of two steps per launch: 0 (default) one wavefront per work item (strip x

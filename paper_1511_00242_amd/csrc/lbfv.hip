@@ -63,7 +63,7 @@ struct HostCase {
     RefState ref() const { return RefState{rho0, rho0 * u0[0] / c, rho0 * u0[1] / c}; }
 };
 
-// Which kernels advance a context: the patch form where the rule of use_patch says so, until
+// Which kernels advance a context: the forms that plan_advance picks by the size of the mesh, until
 // the caller sets a march shape (FORM_MARCH) or the autotuner picks one of the two.
 enum Form { FORM_AUTO = 0, FORM_MARCH = 1, FORM_PATCH = 2 };
 
@@ -95,8 +95,10 @@ struct lbfv_ctx {
     bool has_state = false;
     bool unstable = false;
     int64_t steps = 0, steps_at_check = 0;
-    int rows = 0, wpb = 4;
+    int rows = 0, wpb = 4;           // rows 0: not set, default_rows decides
     int pairs = 0;                   // two steps per launch, periodic mesh: a pair of waves per item
+    int rows_of[2][5][2] = {};       // default_rows of the BKG / other kernels, time block and pairs (0: not asked yet)
+    bool pinned = false;             // a program may hold captured work on the state's layout: keep it
     // graphs of `gsteps` launches, per scheme (+4 per further step per launch) and starting buffer
     int gsteps = 32;
     // (16 + scheme: the patch form)
@@ -643,12 +645,36 @@ std::vector<int> balanced_rows(const HostCase &h, int slots, int strip, int kmax
     return out;
 }
 
-int default_rows(const HostCase &h, int scheme, int wpb) {
+// Row-block height of a march whose height was not set.  One step per launch: 8 or 16 rows, and
+// on large meshes one round of resident waves.  Several steps per launch: k whole rounds of
+// resident work items (waves, pairs or chains), k such that the rows a slot marches are fewest,
+// each item's own and the 3 tb that fill and drain its levels.  That is the autotuner's choice to
+// within a few rows (4096^2 FP64 DUGKS, chains of four: 205 rows; 1024^2: 40; 512^2: 11), where
+// the one-step heights of 8 and 16 rows ran a chain of four on 1536^2 FP16 at 35.2 us a step
+// against 24.0.
+int default_rows(const HostCase &h, int scheme, int wpb, int tb = 1, bool pairs = false) {
     const int64_t cells = (int64_t)h.nx * h.ny;
+    const bool bnd = !(h.periodic_x() && h.periodic_y()), ref = ref_terms(h);
+    if (tb >= 2) {
+        const int slots = tb >= 3 ? resident_waves(stepc_fn_variant(h.variant, scheme, tb, ref), tb) / tb
+                          : pairs ? resident_waves(step2p_fn_variant(h.variant, scheme, bnd, ref), 2) / 2
+                                  : resident_waves(step2_fn_variant(h.variant, scheme, bnd, ref), wpb);
+        const int strip = SLOTS - 2 * tb, nstrips = (h.nx + strip - 1) / strip;
+        int best = 0, least = 0;
+        for (int k = 1; k <= 8; ++k) {
+            const int blocks = std::min(k * slots / nstrips, h.ny);
+            if (blocks < 1) continue;
+            const int rows = (h.ny + blocks - 1) / blocks, cost = k * (rows + 3 * tb);
+            if (!best || cost < least) {
+                best = rows;
+                least = cost;
+            }
+        }
+        if (best) return best;
+    }
     if (cells >= (1 << 22)) {
         // large meshes: one round of resident waves
-        const bool bnd = !(h.periodic_x() && h.periodic_y());
-        auto r = balanced_rows(h, resident_waves(step_fn_variant(h.variant, scheme, bnd, ref_terms(h)), wpb), STRIP1);
+        auto r = balanced_rows(h, resident_waves(step_fn_variant(h.variant, scheme, bnd, ref), wpb), STRIP1);
         if (!r.empty()) return r[0];
         return std::min(64, h.ny);
     }
@@ -794,6 +820,7 @@ int ensure_metrics(lbfv_ctx *c, double ext[4]) {
         HIPCHK(upload_metrics(h, ext, c->stream));
         drop_graphs(c);
         c->plan[0] = c->plan[1] = PatchPlan();   // (the patches depend on the kinds of sides)
+        memset(c->rows_of, 0, sizeof(c->rows_of));
     }
     return LBFV_OK;
 }
@@ -814,19 +841,6 @@ PatchPlan &patch_plan(lbfv_ctx *c, int scheme) {
     if (!p.g.halo) p = best_patch_plan(c->hc, patch_device(is_f64(c->hc.variant), patch_kernel_of(c, scheme)), scheme);
     return p;
 }
-// Whether the patch form advances the context (its metrics are up to date): asked for by the
-// autotuner, or by the size of the mesh where no shape was set.  A stream under capture gets
-// marches: an even number of one-step launches leaves the state in the buffer it started from,
-// which a program that replays what it captured relies on.
-bool use_patch(lbfv_ctx *c, int scheme) {
-    if (c->form == FORM_MARCH) return false;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) (void)hipGetLastError();
-    else if (capture != hipStreamCaptureStatusNone) return false;
-    const HostCase &h = c->hc;
-    if (c->form == FORM_AUTO && (int64_t)h.nx * h.ny > PATCH_CELLS) return false;
-    return patch_plan(c, scheme).waves > 0;
-}
 // grid, workgroup and LDS of a patch launch
 void patch_dims(const lbfv_ctx *c, const PatchPlan &p, dim3 &grid, dim3 &block, unsigned &lds) {
     grid = dim3(p.g.npx * p.g.npy);
@@ -834,8 +848,15 @@ void patch_dims(const lbfv_ctx *c, const PatchPlan &p, dim3 &grid, dim3 &block, 
     lds = (unsigned)(PATCH_LDS * 64 * p.waves * (is_f64(c->hc.variant) ? 8 : 4));
 }
 
-// a launch of two steps with the pair-of-waves form
-bool paired(const lbfv_ctx *c, int tb) { return tb == 2 && c->pairs; }
+// a launch of two steps with the pair-of-waves form (also where no shape was set)
+bool paired(const lbfv_ctx *c, int tb) { return tb == 2 && (c->pairs || c->form == FORM_AUTO); }
+// rows of the row blocks of a launch of tb steps
+int march_rows(lbfv_ctx *c, int scheme, int tb) {
+    if (c->rows > 0) return c->rows;
+    int &rows = c->rows_of[scheme == SCHEME_BKG][tb][paired(c, tb)];
+    if (!rows) rows = default_rows(c->hc, scheme, c->wpb, tb, paired(c, tb));
+    return rows;
+}
 
 // the step kernel of a launch of tb steps: a chain of tb waves per work item (tb = 3, 4;
 // doubly periodic meshes), two steps (in a strip layout of 60 columns or fewer; with or
@@ -936,7 +957,7 @@ int launch_patch(lbfv_ctx *c, int scheme, int parity, const double ext[4], int s
 
 int launch_one(lbfv_ctx *c, int scheme, int parity, const double ext[4], int tb = 1) {
     HostCase &h = c->hc;
-    StepShape sh = step_shape(h, c->rows, c->wpb);
+    StepShape sh = step_shape(h, march_rows(c, scheme, tb), c->wpb);
     StepArgs a;
     int st = launch_args(c, scheme, parity, ext, sh, a);
     if (st) return st;
@@ -949,7 +970,7 @@ int launch_one(lbfv_ctx *c, int scheme, int parity, const double ext[4], int tb 
 // a graph of gsteps launches of tb steps each, in the patch form or as marches
 int build_graph(lbfv_ctx *c, int scheme, int parity0, const double ext[4], int tb, bool patch) {
     HostCase &h = c->hc;
-    StepShape sh = step_shape(h, patch ? 1 : c->rows, c->wpb);
+    StepShape sh = step_shape(h, patch ? 1 : march_rows(c, scheme, tb), c->wpb);
     hipGraph_t g;
     HIPCHK(hipGraphCreate(&g, 0));
     hipGraphNode_t prev = nullptr;
@@ -1112,6 +1133,74 @@ const char *reference_conflict(const HostCase &h) {
     return nullptr;
 }
 
+// Move the current state to the strip layout of w output columns (into the other buffer).
+int set_layout(lbfv_ctx *c, int w) {
+    HostCase &h = c->hc;
+    if (w == h.strip) return LBFV_OK;
+    if (c->has_state) {
+        int st = poll_check(c, true);
+        if (st) return st;
+        HIPCHK(relayout(h, h.cur, w, c->stream));
+        h.cur ^= 1;
+    }
+    h.set_strip(w);
+    drop_graphs(c);
+    return LBFV_OK;
+}
+
+// How a call of n steps advances the context.  per: most steps of a launch.  exact: no shape was
+// asked for, so the call behaves as one-step launches do: checks fall due at their step, and the
+// state ends in the buffer that n launches would leave it in (a program may replay captured work
+// that names that buffer).
+struct Advance {
+    bool patch = false, exact = false;
+    int per = 1;
+};
+// The steps per launch of marches where no shape was set: a chain of four waves on a doubly
+// periodic mesh, a pair of waves with sides.
+int unasked_time_block(const HostCase &h) { return !has_boundary(h) && std::min(h.nx, h.ny) >= 8 ? 4 : 2; }
+// Where no shape was set, meshes up to this size take patches in calls of any length, larger ones
+// in long calls the marches above: the two pass each other near 450^2 cells in FP64 (vortex, DUGKS:
+// 448^2 patches 8.4 us a step, chains 7.1; 384^2 5.6 and 6.4) and 600^2 in FP32 (512^2 5.6 and 7.2;
+// 640^2 10.7 and 8.6), with sides a little above that (cavity FP64 448^2 9.7 and 10.3, 512^2 12.9
+// and 11.1; FP32 640^2 10.6 and 10.9, 768^2 14.3 and 12.6).
+int64_t patch_cells(const HostCase &h) {
+    const bool f64 = is_f64(h.variant);
+    return has_boundary(h) ? (f64 ? 1 << 18 : 1 << 19) : (f64 ? 170000 : 350000);
+}
+constexpr int LONG_CALL = 16;   // steps from which moving the state to another layout pays
+int plan_advance(lbfv_ctx *c, int scheme, int n, Advance &a) {
+    HostCase &h = c->hc;
+    const int64_t cells = (int64_t)h.nx * h.ny;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) (void)hipGetLastError();
+    a.per = h.tblock;
+    if (c->form == FORM_MARCH) return LBFV_OK;
+    a.exact = true;
+    // a stream under capture gets one-step launches
+    if (capture != hipStreamCaptureStatusNone) {
+        c->pinned = true;
+        return LBFV_OK;
+    }
+    // 16-bit storage is rounded after every step unless several per launch were asked for
+    const bool wide = h.variant == V_F64 || h.variant == V_F32;
+    if (c->form == FORM_AUTO && wide && cells > patch_cells(h)) {
+        const int tb = unasked_time_block(h), strip = SLOTS - 2 * tb;
+        if (h.strip == strip || (n >= LONG_CALL && !c->pinned)) {
+            a.per = tb;
+            return set_layout(c, strip);
+        }
+    }
+    // (short calls on larger meshes: patches too, but for FP64 with sides, whose few resident
+    // waves gain nothing there: 1024^2 cavity, three steps of DUGKS, 70 us a step against 68)
+    const int64_t most = has_boundary(h) && h.variant == V_F64 ? patch_cells(h) : PATCH_CELLS;
+    if (c->form == FORM_PATCH || cells <= most) {
+        const PatchPlan &p = patch_plan(c, scheme);
+        a.patch = p.waves > 0;
+        if (a.patch) a.per = p.g.halo;
+    }
+    return LBFV_OK;
+}
 // lbfv_set_time_block, the form of the launches left as it is
 int set_time_block(lbfv_ctx *c, int32_t steps) {
     HostCase &h = c->hc;
@@ -1122,20 +1211,16 @@ int set_time_block(lbfv_ctx *c, int32_t steps) {
         return c->fail(LBFV_EINVAL, "lbfv_set_time_block: 3 or 4 steps per launch need a doubly periodic mesh");
     if (steps >= 3 && (h.nx < 2 * steps || h.ny < 2 * steps))
         return c->fail(LBFV_EINVAL, "lbfv_set_time_block: 3 or 4 steps per launch need at least 2 x steps cells per side");
-    const int w = SLOTS - 2 * steps;   // 62, 60, 58 or 56 output columns per strip
-    if (w != h.strip) {
-        if (c->has_state) {
-            // move the current state into the other buffer in the new layout
-            int st = poll_check(c, true);
-            if (st) return st;
-            HIPCHK(relayout(h, h.cur, w, c->stream));
-            h.cur ^= 1;
-        }
-        h.set_strip(w);
-        drop_graphs(c);
-    }
+    int st = set_layout(c, SLOTS - 2 * steps);   // 62, 60, 58 or 56 output columns per strip
+    if (st) return st;
     h.tblock = steps;
     return LBFV_OK;
+}
+
+// A march control was set: marches in the layout of the time block from here on.
+int take_marches(lbfv_ctx *c) {
+    c->form = FORM_MARCH;
+    return set_layout(c, SLOTS - 2 * c->hc.tblock);
 }
 
 int do_steps(lbfv_ctx *c, int scheme, int32_t n) {
@@ -1157,22 +1242,22 @@ int do_steps(lbfv_ctx *c, int scheme, int32_t n) {
         if ((st = set_time_block(c, 2))) return st;
     }
     current_ext(h, ext);
-    const bool patch = use_patch(c, scheme);
-    if (!patch && c->rows <= 0) c->rows = default_rows(h, scheme, c->wpb);
-    // tblock steps per launch; the steps left over make one launch of fewer steps, in the
-    // same strip layout (every narrower march fits a wider halo's strip).  The patch form
-    // takes up to its halo width of steps per launch.
-    const int per = patch ? patch_plan(c, scheme).g.halo : h.tblock;
+    Advance adv;
+    if ((st = plan_advance(c, scheme, n, adv))) return st;
+    const bool patch = adv.patch;
+    const int per = adv.per;
     auto launch = [&](int steps) {
-        return patch ? launch_patch(c, scheme, h.cur, ext, steps) : launch_one(c, scheme, h.cur, ext, steps);
+        int ls = patch ? launch_patch(c, scheme, h.cur, ext, steps) : launch_one(c, scheme, h.cur, ext, steps);
+        if (!ls) h.cur ^= 1;
+        return ls;
     };
     while (n > 0) {
         int seg = n;
         if (c->check_every > 0) {
-            // the check comes at the first launch boundary at or after check_every steps,
-            // so that a check never splits a launch of `per` steps into shorter ones
+            // the check comes at the first launch boundary at or after check_every steps, so
+            // that a check never splits a launch of `per` steps that was asked for
             int64_t to_check = std::max<int64_t>(c->check_every - (c->steps - c->steps_at_check), 1);
-            if (!patch) to_check = (to_check + per - 1) / per * per;
+            if (!adv.exact) to_check = (to_check + per - 1) / per * per;
             seg = (int)std::min<int64_t>(seg, to_check);
         }
         int left = seg;
@@ -1186,15 +1271,15 @@ int do_steps(lbfv_ctx *c, int scheme, int32_t n) {
             h.cur ^= (c->gsteps & 1);
             left -= per * c->gsteps;
         }
-        for (; left >= per; left -= per) {
-            st = launch(per);
-            if (st) return st;
-            h.cur ^= 1;
-        }
-        if (left > 0) {
-            st = launch(left);
-            if (st) return st;
-            h.cur ^= 1;
+        // The steps left over: launches of `per` steps and one of fewer, in the same strip layout
+        // (every narrower march fits a wider halo's strip); or an even or odd number of launches
+        // as the steps are, none of them shorter than need be.
+        int launches = (left + per - 1) / per;
+        if (adv.exact) launches += (launches ^ left) & 1;
+        for (; launches > 0; --launches) {
+            const int k = adv.exact ? (left + launches - 1) / launches : std::min(per, left);
+            if ((st = launch(k))) return st;
+            left -= k;
         }
         c->steps += seg;
         n -= seg;
@@ -1609,6 +1694,7 @@ int lbfv_totals_device(lbfv_ctx *c, double *dev_out) {
         return c->fail(LBFV_ESTATE, "lbfv_totals_device: the mesh metrics are not on the device yet (step the "
                                     "context or call lbfv_totals once; their upload allocates)");
     static_assert(RED_GRID * RED_N <= SCRATCH_DOUBLES, "scratch too small for the reduction grid");
+    c->pinned = true;   // (it may be captured: its launches name the state's buffer and layout)
     int dev = -1;
     HIPCHK(hipGetDevice(&dev));
     if (dev != c->device) return c->fail(LBFV_EINVAL, "lbfv_totals_device: the context's device must be current");
@@ -1697,6 +1783,8 @@ int lbfv_set_reference_velocity(lbfv_ctx *c, double ux, double uy) {
         HIPCHK(hipGetLastError());
     }
     drop_graphs(c);
+    c->plan[0] = c->plan[1] = PatchPlan();   // (another form of the kernels)
+    memset(c->rows_of, 0, sizeof(c->rows_of));
     return LBFV_OK;
 }
 
@@ -1713,14 +1801,15 @@ int lbfv_set_tile(lbfv_ctx *c, int32_t rows, int32_t wpb) {
         return c->fail(LBFV_EINVAL, "lbfv_set_tile: rows >= 1, waves per block 1, 2 or 4");
     if (rows > 0) c->rows = rows;
     if (wpb > 0) c->wpb = wpb;
-    if (rows > 0 || wpb > 0) c->form = FORM_MARCH;
+    memset(c->rows_of, 0, sizeof(c->rows_of));
     drop_graphs(c);
-    return LBFV_OK;
+    return rows > 0 || wpb > 0 ? take_marches(c) : (int)LBFV_OK;
 }
 
 int lbfv_get_tile(const lbfv_ctx *c, int32_t *rows, int32_t *wpb) {
     if (!c || !rows || !wpb) return LBFV_EINVAL;
-    *rows = c->rows > 0 ? c->rows : default_rows(c->hc, SCHEME_DUGKS, c->wpb);
+    const HostCase &h = c->hc;
+    *rows = c->rows > 0 ? c->rows : default_rows(h, SCHEME_DUGKS, c->wpb, h.sides_set() ? h.tblock : 1, c->pairs);
     *wpb = c->wpb;
     return LBFV_OK;
 }
@@ -1729,9 +1818,8 @@ int lbfv_set_wave_pairs(lbfv_ctx *c, int32_t on) {
     if (!c) return LBFV_EINVAL;
     if (on != 0 && on != 1) return c->fail(LBFV_EINVAL, "lbfv_set_wave_pairs: 0 or 1");
     c->pairs = on;
-    c->form = FORM_MARCH;
     drop_graphs(c);
-    return LBFV_OK;
+    return take_marches(c);
 }
 
 int lbfv_get_wave_pairs(const lbfv_ctx *c, int32_t *on) {
@@ -2752,8 +2840,11 @@ int lbfv_batch_step(lbfv_batch *b, int scheme, int32_t n) {
         b->parity ^= (b->gsteps & 1);
         n -= per * b->gsteps;
     }
-    while (n > 0) {
-        const int k = std::min(n, per);
+    // (patches: an even or odd number of launches as the steps are, like one-step launches)
+    int launches = (n + per - 1) / per;
+    if (patch) launches += (launches ^ n) & 1;
+    for (; launches > 0; --launches) {
+        const int k = patch ? (n + launches - 1) / launches : std::min(n, per);
         st = patch ? batch_launch_patches(b, scheme, b->parity, k) : batch_launch_one(b, scheme, b->parity, k == 2);
         if (st) return st;
         b->parity ^= 1;

@@ -167,3 +167,52 @@ def test_batch_patches_equal_one_step_marches(form):
             for other in outs[1:]:
                 for w, f, g in zip(cases, outs[0], other):
                     assert np.all(np.isfinite(f)) and np.array_equal(f, g), w.name
+
+
+@pytest.mark.parametrize("form,sides,nx,ny", [("f64", None, 420, 410), ("f64", 3, 520, 510),
+                                              ("f32", None, 601, 590), ("f32", 5, 730, 720)])
+def test_unasked_marches_of_several_steps_equal_one_step_marches(form, sides, nx, ny):
+    """The smallest meshes on which a context without a shape moves to several steps per launch
+    in its long calls: short calls before and after, leftover steps, a switch of scheme, and a
+    shape set later."""
+    w = _periodic_workload(nx, ny, 5)
+    if sides is not None:
+        w.bcs = _side_sets(nx)[sides]
+    compute, storage = FORMS[form]
+    plan = [(L.LBFV_DUGKS, 3), (L.LBFV_DUGKS, 37), (L.LBFV_DUGKS, 2), (L.LBFV_BKG, 18), (L.LBFV_BKG, 1)]
+    outs = []
+    for march in (True, False):
+        with L.Context(w.xf, w.yf, w.tau, w.dt, bcs=w.bcs, compute=compute, storage=storage, check_every=10) as ctx:
+            ctx.init_equilibrium(w.rho, w.ux, w.uy)
+            if march:
+                ctx.set_tile(24, 4)
+            for scheme, n in plan:
+                ctx.step(scheme, n)
+            if not march:
+                assert ctx.get_time_block() == 1
+                ctx.set_tile(24, 4)
+            ctx.dugks_step(5)
+            outs.append(ctx.get_f())
+    assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("n", [32, 420])
+def test_captured_totals_follow_steps(n):
+    """lbfv_totals_device captured once and replayed between calls of an even number of steps: the
+    state stays in the buffer and the layout that the captured launches name."""
+    import torch
+    w = I.taylor_green(n)
+    s = torch.cuda.Stream()
+    with L.Context(w.xf, w.yf, w.tau, w.dt, bcs=w.bcs, check_every=0, stream=s.cuda_stream) as ctx:
+        ctx.init_equilibrium(w.rho, w.ux * 30, w.uy * 30 + 0.01)
+        ctx.dugks_step(2)
+        out = torch.zeros(4, dtype=torch.float64, device="cuda")
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            ctx.totals_device(out.data_ptr())
+        for k in (2, 4, 64, 100, 300):
+            ctx.dugks_step(k)
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy()[:3], ctx.totals()), k
