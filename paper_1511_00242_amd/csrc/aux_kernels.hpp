@@ -25,17 +25,23 @@ struct RefState {
     __device__ double F(int a) const { return wgt(a) * (rho0 + (3.0 * (EX[a] * m0x + EY[a] * m0y) + q0(a))); }
 };
 
+// The conversion kernels below handle cells [k0, k0 + n) of the mesh; their host-side arrays hold
+// n values per component, one component after the other.  They lie in pinned host memory that
+// the kernels reach directly: a wave reads or writes 512 contiguous bytes of each component.
+struct CellRange {
+    int64_t k0, n;
+};
+
 // f~ of an equilibrium state (Omega(feq) = 0): x_a = feq_a(rho, u) - F_a, evaluated in FP64
 // and rounded once to the stored type.
 template <typename T, typename S>
-__global__ void init_eq_kernel(StepParams<T> P, int parity, const double *rho, const double *ux,
-                               const double *uy, double inv_c, RefState R) {
-    const int64_t n = (int64_t)P.nx * P.ny;
+__global__ void init_eq_kernel(StepParams<T> P, int parity, CellRange C, const double *in, double inv_c, RefState R) {
+    const int64_t n = C.n;
     S *dst = (S *)P.buf[parity];
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
-        const double r = rho[k], u = ux[k] * inv_c, v = uy[k] * inv_c;
+        const double r = in[k], u = in[n + k] * inv_c, v = in[2 * n + k] * inv_c;
         const double usq15 = 1.5 * (u * u + v * v);
-        S *p = dst + cell_offset(P, k);
+        S *p = dst + cell_offset(P, C.k0 + k);
 #pragma unroll
         for (int a = 0; a < 9; ++a) {
             const double x = dfeq<double>(a, r - R.rho0, r, r * u - R.m0x, r * v - R.m0y, u, v, usq15, R.q0(a));
@@ -49,16 +55,16 @@ __global__ void init_eq_kernel(StepParams<T> P, int parity, const double *rho, c
 // as [3][ny][nx] along t, x, y), then stored as f~ = f + (dt / 2 tau)(f - feq) (Sec. 2.2).
 // Evaluated in FP64 and rounded once to the stored type.
 template <typename T, typename S>
-__global__ void init_ce_kernel(StepParams<T> P, int parity, const double *rho, const double *ux, const double *uy,
-                               const double *drho, const double *dux, const double *duy, double c, double tau,
-                               double dt, RefState R) {
-    const int64_t n = (int64_t)P.nx * P.ny;
+__global__ void init_ce_kernel(StepParams<T> P, int parity, CellRange C, const double *rho, double c, double tau, double dt,
+                               RefState R) {
+    const int64_t n = C.n;
+    const double *ux = rho + n, *uy = rho + 2 * n, *drho = rho + 3 * n, *dux = rho + 6 * n, *duy = rho + 9 * n;
     S *dst = (S *)P.buf[parity];
     const double inv_c = 1.0 / c, k = 0.5 * dt / tau;
     for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n; q += (int64_t)gridDim.x * blockDim.x) {
         const double r = rho[q], u = ux[q] * inv_c, v = uy[q] * inv_c;   // u-hat = u / c
         const double usq15 = 1.5 * (u * u + v * v);
-        S *p = dst + cell_offset(P, q);
+        S *p = dst + cell_offset(P, C.k0 + q);
 #pragma unroll
         for (int a = 0; a < 9; ++a) {
             // directional derivative D = d_t + c (e_x d_x + e_y d_y)
@@ -78,11 +84,11 @@ __global__ void init_ce_kernel(StepParams<T> P, int parity, const double *rho, c
 
 // host-layout FP64 f~ [9][ny][nx] -> stored deviations
 template <typename T, typename S>
-__global__ void set_f_kernel(StepParams<T> P, int parity, const double *f, RefState R) {
-    const int64_t n = (int64_t)P.nx * P.ny;
+__global__ void set_f_kernel(StepParams<T> P, int parity, CellRange C, const double *f, RefState R) {
+    const int64_t n = C.n;
     S *dst = (S *)P.buf[parity];
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
-        S *p = dst + cell_offset(P, k);
+        S *p = dst + cell_offset(P, C.k0 + k);
 #pragma unroll
         for (int a = 0; a < 9; ++a) {
             p[a * P.plane] = Storage<S>::store((T)(f[a * n + k] - R.F(a)), a);
@@ -91,11 +97,11 @@ __global__ void set_f_kernel(StepParams<T> P, int parity, const double *f, RefSt
 }
 
 template <typename T, typename S>
-__global__ void get_f_kernel(StepParams<T> P, int parity, double *f, RefState R) {
-    const int64_t n = (int64_t)P.nx * P.ny;
+__global__ void get_f_kernel(StepParams<T> P, int parity, CellRange C, double *f, RefState R) {
+    const int64_t n = C.n;
     const S *src = (const S *)P.buf[parity];
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
-        const S *p = src + cell_offset(P, k);
+        const S *p = src + cell_offset(P, C.k0 + k);
 #pragma unroll
         for (int a = 0; a < 9; ++a) {
             f[a * n + k] = (double)Storage<S>::load(p[a * P.plane], a) + R.F(a);
@@ -125,16 +131,15 @@ __device__ __forceinline__ bool cell_moments64(const StepParams<T> &P, const S *
 }
 
 template <typename T, typename S>
-__global__ void moments_kernel(StepParams<T> P, int parity, double *rho, double *ux, double *uy, RefState R,
-                               double c) {
-    const int64_t n = (int64_t)P.nx * P.ny;
+__global__ void moments_kernel(StepParams<T> P, int parity, CellRange C, double *out, RefState R, double c) {
+    const int64_t n = C.n;
     const S *src = (const S *)P.buf[parity];
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
         double r, u, v;
-        cell_moments64(P, src, k, R, c, r, u, v);
-        rho[k] = r;
-        ux[k] = u;
-        uy[k] = v;
+        cell_moments64(P, src, C.k0 + k, R, c, r, u, v);
+        out[k] = r;
+        out[n + k] = u;
+        out[2 * n + k] = v;
     }
 }
 

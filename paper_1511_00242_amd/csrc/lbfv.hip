@@ -17,6 +17,7 @@
 #include <mutex>
 #include <sstream>
 #include <string>
+#include <thread>
 #include <vector>
 
 using namespace lbfv;
@@ -44,10 +45,12 @@ struct HostCase {
     size_t esize = 8;
     void *buf[2] = {nullptr, nullptr};
     bool own = true;
+    bool joint = false;       // both buffers lie in one allocation, buf[0]'s
     int cur = 0;              // buffer holding the current state
-    void *d_xm = nullptr, *d_ym = nullptr;   // metrics in the compute type
+    void *d_xm = nullptr, *d_ym = nullptr;   // metrics in the compute type (d_xm owns the block of all four)
     double *d_dx = nullptr, *d_dy = nullptr; // cell sizes (FP64) for volumes
     bool metrics_dirty = true;
+    double ext[4] = {0, 0, 0, 0};   // ghost extrapolation factors, of the uploaded metrics
 
     // buffers fit the state in every strip layout (the narrowest strip pads most)
     size_t buffer_bytes() const { return (size_t)padded_pitch(nx, STRIP4) * ny * 9 * esize; }
@@ -85,6 +88,126 @@ struct PatchPlan {
         }                                                                                       \
     } while (0)
 
+// Fields between caller-owned (pageable) host arrays and the state.  The conversion kernels read
+// and write pinned host memory directly, in chunks of cells; a chunk is copied between the
+// caller's arrays and its slot of the buffer while other chunks are with the GPU.  Large fields
+// take several threads, each with two slots and its own chunks: one thread copies 5 to 10 GB/s
+// (the arrays' pages are often touched for the first time), the GPU's link 50.  The buffer and
+// its events belong to one context or batch and are kept until it is destroyed.
+class Transfer {
+public:
+    // f(range, slot): enqueue the conversion kernel of `range` on the stream
+    template <typename F>
+    hipError_t run(bool up, int64_t cells, const std::vector<double *> &arrays, hipStream_t stream, F f) {
+        const int64_t width = 8 * (int64_t)arrays.size(), total = cells * width;
+        // chunks of about 1 MiB; a thread per 2 MiB, at most 8 and half the CPUs
+        int threads = (int)std::min<int64_t>({total >> 21, 8, (int64_t)std::thread::hardware_concurrency() / 2});
+        threads = std::max(threads, 1);
+        const int64_t chunk = threads == 1 && total <= kBuffer / 2 ? cells : std::max<int64_t>(1, (1 << 20) / width);
+        if (chunk == cells) {
+            // one chunk: the stream itself is waited for
+            hipError_t e = reserve((size_t)std::max(total, (int64_t)4096), 0);
+            if (e != hipSuccess) return e;
+            if (up) copy(true, arrays, 0, cells, slot(0, total));
+            f(CellRange{0, cells}, slot(0, total));
+            e = hipGetLastError();
+            const hipError_t done = hipStreamSynchronize(stream);
+            if (e == hipSuccess) e = done;
+            if (e == hipSuccess && !up) copy(false, arrays, 0, cells, slot(0, total));
+            return e;
+        }
+        hipError_t e = reserve((size_t)std::min<int64_t>(2 * threads * chunk * width, total), 2 * threads);
+        if (e != hipSuccess) return e;
+        int dev = 0;
+        if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+        std::vector<hipError_t> result(threads, hipSuccess);
+        // thread t: chunks t, t + threads, ..., alternating between its two slots
+        auto work = [&](int t, int stride) {
+            hipError_t &r = result[t];
+            if (t && (r = hipSetDevice(dev)) != hipSuccess) return;
+            int64_t from[2] = {0, 0}, count[2] = {0, 0};
+            int turn = 0;
+            auto finish = [&](int k) {
+                if (!count[k] || r != hipSuccess) return;
+                if ((r = hipEventSynchronize(events_[2 * t + k])) != hipSuccess) return;
+                if (!up) copy(false, arrays, from[k], count[k], slot(2 * t + k, chunk * width));
+                count[k] = 0;
+            };
+            for (int64_t k0 = t * chunk; k0 < cells && r == hipSuccess; k0 += stride * chunk, turn ^= 1) {
+                finish(turn);
+                if (r != hipSuccess) break;
+                double *buf = slot(2 * t + turn, chunk * width);
+                from[turn] = k0;
+                count[turn] = std::min(chunk, cells - k0);
+                if (up) copy(true, arrays, k0, count[turn], buf);
+                f(CellRange{k0, count[turn]}, buf);
+                if ((r = hipGetLastError()) == hipSuccess) r = hipEventRecord(events_[2 * t + turn], stream);
+            }
+            finish(turn);
+            finish(turn ^ 1);
+        };
+        std::vector<std::thread> pool;
+        int started = 1;
+        try {
+            pool.reserve(threads);
+            for (; started < threads; ++started) pool.emplace_back(work, started, threads);
+        } catch (...) {
+        }
+        work(0, threads);
+        for (auto &th : pool) th.join();
+        // chunks of threads that could not be started
+        for (int t = started; t < threads; ++t) work(t, threads);
+        // an error leaves kernels that may still use the buffer
+        const hipError_t done = hipStreamSynchronize(stream);
+        for (hipError_t r : result)
+            if (r != hipSuccess) return r;
+        return done;
+    }
+    void release() {
+        if (pinned_) (void)hipHostFree(pinned_);
+        for (auto e : events_) (void)hipEventDestroy(e);
+        pinned_ = nullptr;
+        size_ = 0;
+        events_.clear();
+    }
+
+private:
+    static constexpr int64_t kBuffer = 16 << 20;   // most bytes kept
+    char *pinned_ = nullptr;
+    size_t size_ = 0;
+    std::vector<hipEvent_t> events_;
+
+    double *slot(int k, int64_t bytes) const {
+        return (double *)(pinned_ + std::min<int64_t>(k * bytes, (int64_t)size_ - bytes));
+    }
+    hipError_t reserve(size_t bytes, int events) {
+        hipError_t e;
+        if (bytes > size_) {
+            if (pinned_) (void)hipHostFree(pinned_);
+            pinned_ = nullptr;
+            size_ = 0;
+            if ((e = hipHostMalloc((void **)&pinned_, bytes, hipHostMallocDefault)) != hipSuccess) {
+                (void)hipGetLastError();
+                pinned_ = nullptr;
+                return e;
+            }
+            size_ = bytes;
+        }
+        while ((int)events_.size() < events) {
+            hipEvent_t ev;
+            if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return e;
+            events_.push_back(ev);
+        }
+        return hipSuccess;
+    }
+    static void copy(bool up, const std::vector<double *> &arrays, int64_t k0, int64_t n, double *buf) {
+        for (size_t a = 0; a < arrays.size(); ++a) {
+            if (up) memcpy(buf + a * n, arrays[a] + k0, n * 8);
+            else memcpy(arrays[a] + k0, buf + a * n, n * 8);
+        }
+    }
+};
+
 }  // namespace
 
 struct lbfv_ctx {
@@ -117,6 +240,7 @@ struct lbfv_ctx {
     hipEvent_t p2b_event[4] = {};
     bool p2b_pending[4] = {};
     std::vector<char> p2b_last[4];
+    Transfer transfer;
     std::string last_error;
 
     int fail(int status, const std::string &msg) {
@@ -152,6 +276,7 @@ struct lbfv_batch {
         PatchItem *d_items = nullptr;
     } patches[2];
     bool has_state = false;
+    Transfer transfer;
     std::string last_error;
     int fail(int status, const std::string &msg) {
         last_error = msg;
@@ -286,42 +411,68 @@ hipError_t upload_metrics(HostCase &h, double ext[4], hipStream_t s) {
     std::vector<double> mx, my, sx, sy;
     axis_metrics(h.xf, h.periodic_x(), h.dt, h.c, mx, ext[SIDE_W], ext[SIDE_E], sx);
     axis_metrics(h.yf, h.periodic_y(), h.dt, h.c, my, ext[SIDE_S], ext[SIDE_N], sy);
+    // one block on the device, x and y metrics, then cell sizes, and one copy into it
     const size_t tsz = is_f64(h.variant) ? 8 : 4;
-    hipError_t e;
-    if (!h.d_xm) {
-        if ((e = hipMalloc(&h.d_xm, mx.size() * tsz)) != hipSuccess) return e;
-        if ((e = hipMalloc(&h.d_ym, my.size() * tsz)) != hipSuccess) return e;
-        if ((e = hipMalloc((void **)&h.d_dx, sx.size() * 8)) != hipSuccess) return e;
-        if ((e = hipMalloc((void **)&h.d_dy, sy.size() * 8)) != hipSuccess) return e;
-    }
+    const size_t nmx = mx.size() * tsz, nmy = my.size() * tsz, at_dx = (nmx + nmy + 7) / 8 * 8;
+    std::vector<char> block(at_dx + (sx.size() + sy.size()) * 8);
     if (tsz == 8) {
-        if ((e = hipMemcpyAsync(h.d_xm, mx.data(), mx.size() * 8, hipMemcpyHostToDevice, s)) != hipSuccess) return e;
-        if ((e = hipMemcpyAsync(h.d_ym, my.data(), my.size() * 8, hipMemcpyHostToDevice, s)) != hipSuccess) return e;
+        memcpy(block.data(), mx.data(), nmx);
+        memcpy(block.data() + nmx, my.data(), nmy);
     } else {
         std::vector<float> fx, fy;
         copy_as(mx, fx);
         copy_as(my, fy);
-        if ((e = hipMemcpyAsync(h.d_xm, fx.data(), fx.size() * 4, hipMemcpyHostToDevice, s)) != hipSuccess) return e;
-        if ((e = hipMemcpyAsync(h.d_ym, fy.data(), fy.size() * 4, hipMemcpyHostToDevice, s)) != hipSuccess) return e;
+        memcpy(block.data(), fx.data(), nmx);
+        memcpy(block.data() + nmx, fy.data(), nmy);
     }
-    if ((e = hipMemcpyAsync(h.d_dx, sx.data(), sx.size() * 8, hipMemcpyHostToDevice, s)) != hipSuccess) return e;
-    if ((e = hipMemcpyAsync(h.d_dy, sy.data(), sy.size() * 8, hipMemcpyHostToDevice, s)) != hipSuccess) return e;
-    // the host vectors die here: wait for the copies
+    memcpy(block.data() + at_dx, sx.data(), sx.size() * 8);
+    memcpy(block.data() + at_dx + sx.size() * 8, sy.data(), sy.size() * 8);
+    hipError_t e;
+    if (!h.d_xm) {
+        if ((e = hipMalloc(&h.d_xm, block.size())) != hipSuccess) return e;
+        h.d_ym = (char *)h.d_xm + nmx;
+        h.d_dx = (double *)((char *)h.d_xm + at_dx);
+        h.d_dy = h.d_dx + sx.size();
+    }
+    if ((e = hipMemcpyAsync(h.d_xm, block.data(), block.size(), hipMemcpyHostToDevice, s)) != hipSuccess) return e;
+    // the host block dies here: wait for the copy
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
     h.metrics_dirty = false;
+    memcpy(h.ext, ext, sizeof(h.ext));
     return hipSuccess;
 }
 
-void free_case(HostCase &h) {
+// The two state buffers of a case, zeroed (the pad slots are never read by the step, but are kept
+// defined); small ones in one allocation.
+hipError_t allocate_buffers(HostCase &h, hipStream_t s) {
+    const size_t bytes = (h.buffer_bytes() + 255) / 256 * 256;
+    h.joint = bytes <= (16 << 20);
+    hipError_t e = hipMalloc(&h.buf[0], h.joint ? 2 * bytes : bytes);
+    if (e == hipSuccess && h.joint) h.buf[1] = (char *)h.buf[0] + bytes;
+    if (e == hipSuccess && !h.joint) e = hipMalloc(&h.buf[1], bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        if (h.buf[0]) (void)hipFree(h.buf[0]);
+        h.buf[0] = h.buf[1] = nullptr;
+        return e;
+    }
+    h.own = true;
+    e = hipMemsetAsync(h.buf[0], 0, h.joint ? 2 * bytes : bytes, s);
+    if (e == hipSuccess && !h.joint) e = hipMemsetAsync(h.buf[1], 0, bytes, s);
+    return e;
+}
+void free_buffers(HostCase &h) {
     if (h.own) {
         if (h.buf[0]) (void)hipFree(h.buf[0]);
-        if (h.buf[1]) (void)hipFree(h.buf[1]);
+        if (h.buf[1] && !h.joint) (void)hipFree(h.buf[1]);
     }
     h.buf[0] = h.buf[1] = nullptr;
+    h.joint = false;
+}
+
+void free_case(HostCase &h) {
+    free_buffers(h);
     if (h.d_xm) (void)hipFree(h.d_xm);
-    if (h.d_ym) (void)hipFree(h.d_ym);
-    if (h.d_dx) (void)hipFree(h.d_dx);
-    if (h.d_dy) (void)hipFree(h.d_dy);
     h.d_xm = h.d_ym = nullptr;
     h.d_dx = h.d_dy = nullptr;
 }
@@ -798,17 +949,9 @@ void drop_graphs(lbfv_ctx *c) {
 int ensure_buffers(lbfv_ctx *c) {
     HostCase &h = c->hc;
     if (h.buf[0]) return LBFV_OK;
-    const size_t bytes = h.buffer_bytes();
-    if (hipMalloc(&h.buf[0], bytes) != hipSuccess || hipMalloc(&h.buf[1], bytes) != hipSuccess) {
-        if (h.buf[0]) (void)hipFree(h.buf[0]);
-        h.buf[0] = h.buf[1] = nullptr;
-        (void)hipGetLastError();
-        return c->fail(LBFV_ENOMEM, "cannot allocate the two state buffers");
-    }
-    h.own = true;
-    // padding columns are never read by the step, but keep them defined
-    HIPCHK(hipMemsetAsync(h.buf[0], 0, bytes, c->stream));
-    HIPCHK(hipMemsetAsync(h.buf[1], 0, bytes, c->stream));
+    const hipError_t e = allocate_buffers(h, c->stream);
+    if (!h.buf[0]) return c->fail(LBFV_ENOMEM, "cannot allocate the two state buffers");
+    HIPCHK(e);
     drop_graphs(c);
     return LBFV_OK;
 }
@@ -825,8 +968,12 @@ int ensure_metrics(lbfv_ctx *c, double ext[4]) {
     return LBFV_OK;
 }
 
-// current extrapolation factors (recomputed on the host; cheap)
+// current extrapolation factors (of the uploaded metrics, or formed on the host)
 void current_ext(const HostCase &h, double ext[4]) {
+    if (!h.metrics_dirty) {
+        memcpy(ext, h.ext, sizeof(h.ext));
+        return;
+    }
     std::vector<double> m, s;
     axis_metrics(h.xf, h.periodic_x(), h.dt, h.c, m, ext[SIDE_W], ext[SIDE_E], s);
     axis_metrics(h.yf, h.periodic_y(), h.dt, h.c, m, ext[SIDE_S], ext[SIDE_N], s);
@@ -1291,45 +1438,51 @@ int do_steps(lbfv_ctx *c, int scheme, int32_t n) {
     return LBFV_OK;
 }
 
-template <typename T, typename S>
-int ce_kernel_t(lbfv_ctx *c, const double *d) {
-    HostCase &h = c->hc;
-    double ext[4];
-    current_ext(h, ext);
-    StepParams<T> P = make_params<T>(h, ext);
-    const int64_t n = (int64_t)h.nx * h.ny;
-    const int blocks = (int)std::min<int64_t>((n + 255) / 256, 8192);
-    hipLaunchKernelGGL((init_ce_kernel<T, S>), dim3(blocks), dim3(256), 0, c->stream, P, h.cur, d, d + n, d + 2 * n,
-                       d + 3 * n, d + 6 * n, d + 9 * n, h.c, h.tau, h.dt, h.ref());
-    HIPCHK(hipGetLastError());
-    return LBFV_OK;
-}
+// ------------------------------------------------------------------ fields to and from the host
+enum Field { F_INIT_EQ, F_INIT_CE, F_SET_F, F_GET_F, F_MOMENTS };
 
 template <typename T, typename S>
-int state_kernel_t(lbfv_ctx *c, int which, const double *d0, const double *d1, const double *d2, double *dout) {
-    HostCase &h = c->hc;
-    double ext[4];
-    current_ext(h, ext);
-    StepParams<T> P = make_params<T>(h, ext);
-    const int64_t n = (int64_t)h.nx * h.ny;
-    const int blocks = (int)std::min<int64_t>((n + 255) / 256, 8192);
+void launch_field(const HostCase &h, const StepParams<T> &P, int parity, Field which, CellRange C, double *buf,
+                  hipStream_t stream) {
+    const dim3 grid((unsigned)std::min<int64_t>((C.n + 255) / 256, 8192)), block(256);
+    const RefState R = h.ref();
     switch (which) {
-    case 0: hipLaunchKernelGGL((init_eq_kernel<T, S>), dim3(blocks), dim3(256), 0, c->stream, P, h.cur, d0, d1, d2, 1.0 / h.c, h.ref()); break;
-    case 1: hipLaunchKernelGGL((set_f_kernel<T, S>), dim3(blocks), dim3(256), 0, c->stream, P, h.cur, d0, h.ref()); break;
-    case 2: hipLaunchKernelGGL((get_f_kernel<T, S>), dim3(blocks), dim3(256), 0, c->stream, P, h.cur, dout, h.ref()); break;
-    default: hipLaunchKernelGGL((moments_kernel<T, S>), dim3(blocks), dim3(256), 0, c->stream, P, h.cur, dout, dout + n, dout + 2 * n, h.ref(), h.c); break;
+    case F_INIT_EQ: hipLaunchKernelGGL((init_eq_kernel<T, S>), grid, block, 0, stream, P, parity, C, buf, 1.0 / h.c, R); break;
+    case F_INIT_CE: hipLaunchKernelGGL((init_ce_kernel<T, S>), grid, block, 0, stream, P, parity, C, buf, h.c, h.tau, h.dt, R); break;
+    case F_SET_F: hipLaunchKernelGGL((set_f_kernel<T, S>), grid, block, 0, stream, P, parity, C, buf, R); break;
+    case F_GET_F: hipLaunchKernelGGL((get_f_kernel<T, S>), grid, block, 0, stream, P, parity, C, buf, R); break;
+    default: hipLaunchKernelGGL((moments_kernel<T, S>), grid, block, 0, stream, P, parity, C, buf, R, h.c); break;
     }
-    HIPCHK(hipGetLastError());
-    return LBFV_OK;
 }
 
-int state_kernel(lbfv_ctx *c, int which, const double *d0, const double *d1, const double *d2, double *dout) {
-    switch (c->hc.variant) {
-    case V_F64: return state_kernel_t<double, double>(c, which, d0, d1, d2, dout);
-    case V_F32: return state_kernel_t<float, float>(c, which, d0, d1, d2, dout);
-    case V_BF16: return state_kernel_t<float, __bf16>(c, which, d0, d1, d2, dout);
-    default: return state_kernel_t<float, _Float16>(c, which, d0, d1, d2, dout);
-    }
+// Move fields between the caller's arrays (one value per cell each) and the state in
+// buf[parity]; the stream is synchronised.
+hipError_t move_fields(const HostCase &h, int parity, Transfer &t, hipStream_t stream, Field which,
+                       const std::vector<double *> &arrays) {
+    double ext[4];
+    current_ext(h, ext);
+    StepParams<double> pd;
+    StepParams<float> pf;
+    if (is_f64(h.variant)) pd = make_params<double>(h, ext);
+    else pf = make_params<float>(h, ext);
+    return t.run(which < F_GET_F, (int64_t)h.nx * h.ny, arrays, stream, [&](CellRange C, double *buf) {
+        switch (h.variant) {
+        case V_F64: launch_field<double, double>(h, pd, parity, which, C, buf, stream); break;
+        case V_F32: launch_field<float, float>(h, pf, parity, which, C, buf, stream); break;
+        case V_BF16: launch_field<float, __bf16>(h, pf, parity, which, C, buf, stream); break;
+        default: launch_field<float, _Float16>(h, pf, parity, which, C, buf, stream); break;
+        }
+    });
+}
+// `count` component arrays of one [count][ny][nx] array
+void add_components(std::vector<double *> &arrays, const double *a, int count, const HostCase &h) {
+    for (int k = 0; k < count; ++k) arrays.push_back(const_cast<double *>(a) + (int64_t)k * h.nx * h.ny);
+}
+template <typename Owner>
+int moved(Owner *o, hipError_t e, const char *what) {
+    if (e == hipSuccess) return LBFV_OK;
+    if (e == hipErrorOutOfMemory) return o->fail(LBFV_ENOMEM, std::string(what) + ": cannot allocate the transfer buffer");
+    return o->fail(LBFV_EHIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
 template <typename T, typename S>
@@ -1342,12 +1495,14 @@ void reref_t(lbfv_ctx *c, const RefState &from, const RefState &to) {
     hipLaunchKernelGGL((reref_kernel<T, S>), dim3(blocks), dim3(256), 0, c->stream, P, h.cur, from, to);
 }
 
-// device staging buffer of `count` doubles (freed by the caller)
-int staging(lbfv_ctx *c, size_t count, double **p) {
-    if (hipMalloc((void **)p, count * sizeof(double)) != hipSuccess) {
-        (void)hipGetLastError();
-        return c->fail(LBFV_ENOMEM, "cannot allocate the staging buffer");
-    }
+// a new state given by the caller's arrays
+int new_state(lbfv_ctx *c, Field which, const std::vector<double *> &arrays, const char *what) {
+    int st = ensure_buffers(c);
+    if (!st) st = moved(c, move_fields(c->hc, c->hc.cur, c->transfer, c->stream, which, arrays), what);
+    if (st) return st;
+    c->has_state = true;
+    c->unstable = false;
+    c->uprev_valid = false;
     return LBFV_OK;
 }
 
@@ -1445,6 +1600,7 @@ int lbfv_destroy(lbfv_ctx *c) {
     if (c->h_out) (void)hipHostFree(c->h_out);
     if (c->d_uprev) (void)hipFree(c->d_uprev);
     if (c->check_event) (void)hipEventDestroy(c->check_event);
+    c->transfer.release();
     if (c->d_p2b) (void)hipFree(c->d_p2b);
     if (c->h_p2b) (void)hipHostFree(c->h_p2b);
     for (auto e : c->p2b_event)
@@ -1517,10 +1673,7 @@ int lbfv_bind_buffers(lbfv_ctx *c, void *a, void *b, size_t bytes) {
     if (bytes < c->hc.buffer_bytes()) return c->fail(LBFV_EINVAL, "lbfv_bind_buffers: buffers too small");
     HIPCHK(hipStreamSynchronize(c->stream));
     HostCase &h = c->hc;
-    if (h.own) {
-        if (h.buf[0]) (void)hipFree(h.buf[0]);
-        if (h.buf[1]) (void)hipFree(h.buf[1]);
-    }
+    free_buffers(h);
     h.buf[0] = a;
     h.buf[1] = b;
     h.own = false;
@@ -1535,27 +1688,9 @@ int lbfv_bind_buffers(lbfv_ctx *c, void *a, void *b, size_t bytes) {
 int lbfv_init_equilibrium(lbfv_ctx *c, const double *rho, const double *ux, const double *uy) {
     if (!c) return LBFV_EINVAL;
     if (!rho || !ux || !uy) return c->fail(LBFV_EINVAL, "lbfv_init_equilibrium: NULL field");
-    int st = ensure_buffers(c);
-    if (st) return st;
-    HostCase &h = c->hc;
-    const int64_t n = (int64_t)h.nx * h.ny;
-    double *d;
-    st = staging(c, 3 * n, &d);
-    if (st) return st;
-    hipError_t e = hipMemcpyAsync(d, rho, n * 8, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(d + n, ux, n * 8, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(d + 2 * n, uy, n * 8, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) {
-        st = state_kernel(c, 0, d, d + n, d + 2 * n, nullptr);
-        e = hipStreamSynchronize(c->stream);
-    }
-    (void)hipFree(d);
-    if (st) return st;
-    if (e != hipSuccess) return c->fail(LBFV_EHIP, std::string("init_equilibrium: ") + hipGetErrorString(e));
-    c->has_state = true;
-    c->unstable = false;
-    c->uprev_valid = false;
-    return LBFV_OK;
+    std::vector<double *> a;
+    for (const double *f : {rho, ux, uy}) add_components(a, f, 1, c->hc);
+    return new_state(c, F_INIT_EQ, a, "init_equilibrium");
 }
 
 int lbfv_init_chapman_enskog(lbfv_ctx *c, const double *rho, const double *ux, const double *uy,
@@ -1563,78 +1698,27 @@ int lbfv_init_chapman_enskog(lbfv_ctx *c, const double *rho, const double *ux, c
     if (!c) return LBFV_EINVAL;
     if (!rho || !ux || !uy || !drho || !dux || !duy)
         return c->fail(LBFV_EINVAL, "lbfv_init_chapman_enskog: NULL field");
-    int st = ensure_buffers(c);
-    if (st) return st;
-    HostCase &h = c->hc;
-    const int64_t n = (int64_t)h.nx * h.ny;
-    double *d;
-    st = staging(c, 12 * n, &d);
-    if (st) return st;
-    const double *src[6] = {rho, ux, uy, drho, dux, duy};
-    const int64_t off[6] = {0, n, 2 * n, 3 * n, 6 * n, 9 * n};
-    const int64_t cnt[6] = {n, n, n, 3 * n, 3 * n, 3 * n};
-    hipError_t e = hipSuccess;
-    for (int i = 0; i < 6 && e == hipSuccess; ++i)
-        e = hipMemcpyAsync(d + off[i], src[i], cnt[i] * 8, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) {
-        switch (h.variant) {
-        case V_F64: st = ce_kernel_t<double, double>(c, d); break;
-        case V_F32: st = ce_kernel_t<float, float>(c, d); break;
-        case V_BF16: st = ce_kernel_t<float, __bf16>(c, d); break;
-        default: st = ce_kernel_t<float, _Float16>(c, d); break;
-        }
-        e = hipStreamSynchronize(c->stream);
-    }
-    (void)hipFree(d);
-    if (st) return st;
-    if (e != hipSuccess) return c->fail(LBFV_EHIP, std::string("init_chapman_enskog: ") + hipGetErrorString(e));
-    c->has_state = true;
-    c->unstable = false;
-    c->uprev_valid = false;
-    return LBFV_OK;
+    std::vector<double *> a;
+    for (const double *f : {rho, ux, uy}) add_components(a, f, 1, c->hc);
+    for (const double *f : {drho, dux, duy}) add_components(a, f, 3, c->hc);
+    return new_state(c, F_INIT_CE, a, "init_chapman_enskog");
 }
 
 int lbfv_set_f(lbfv_ctx *c, const double *f) {
     if (!c) return LBFV_EINVAL;
     if (!f) return c->fail(LBFV_EINVAL, "lbfv_set_f: NULL array");
-    int st = ensure_buffers(c);
-    if (st) return st;
-    HostCase &h = c->hc;
-    const int64_t n = (int64_t)h.nx * h.ny;
-    double *d;
-    st = staging(c, 9 * n, &d);
-    if (st) return st;
-    hipError_t e = hipMemcpyAsync(d, f, 9 * n * 8, hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) {
-        st = state_kernel(c, 1, d, nullptr, nullptr, nullptr);
-        e = hipStreamSynchronize(c->stream);
-    }
-    (void)hipFree(d);
-    if (st) return st;
-    if (e != hipSuccess) return c->fail(LBFV_EHIP, std::string("set_f: ") + hipGetErrorString(e));
-    c->has_state = true;
-    c->unstable = false;
-    c->uprev_valid = false;
-    return LBFV_OK;
+    std::vector<double *> a;
+    add_components(a, f, 9, c->hc);
+    return new_state(c, F_SET_F, a, "set_f");
 }
 
 int lbfv_get_f(lbfv_ctx *c, double *f) {
     if (!c) return LBFV_EINVAL;
     if (!f) return c->fail(LBFV_EINVAL, "lbfv_get_f: NULL array");
     if (!c->has_state) return c->fail(LBFV_ESTATE, "no state");
-    HostCase &h = c->hc;
-    const int64_t n = (int64_t)h.nx * h.ny;
-    double *d;
-    int st = staging(c, 9 * n, &d);
-    if (st) return st;
-    st = state_kernel(c, 2, nullptr, nullptr, nullptr, d);
-    hipError_t e = hipSuccess;
-    if (!st) e = hipMemcpyAsync(f, d, 9 * n * 8, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    (void)hipFree(d);
-    if (st) return st;
-    if (e != hipSuccess) return c->fail(LBFV_EHIP, std::string("get_f: ") + hipGetErrorString(e));
-    return LBFV_OK;
+    std::vector<double *> a;
+    add_components(a, f, 9, c->hc);
+    return moved(c, move_fields(c->hc, c->hc.cur, c->transfer, c->stream, F_GET_F, a), "get_f");
 }
 
 int dugks_step(lbfv_ctx *c, int32_t n) { return do_steps(c, SCHEME_DUGKS, n); }
@@ -1649,21 +1733,7 @@ int lbfv_moments(lbfv_ctx *c, double *rho, double *ux, double *uy) {
     if (!c) return LBFV_EINVAL;
     if (!rho || !ux || !uy) return c->fail(LBFV_EINVAL, "lbfv_moments: NULL output");
     if (!c->has_state) return c->fail(LBFV_ESTATE, "no state");
-    HostCase &h = c->hc;
-    const int64_t n = (int64_t)h.nx * h.ny;
-    double *d;
-    int st = staging(c, 3 * n, &d);
-    if (st) return st;
-    st = state_kernel(c, 3, nullptr, nullptr, nullptr, d);
-    hipError_t e = hipSuccess;
-    if (!st) e = hipMemcpyAsync(rho, d, n * 8, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(ux, d + n, n * 8, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(uy, d + 2 * n, n * 8, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    (void)hipFree(d);
-    if (st) return st;
-    if (e != hipSuccess) return c->fail(LBFV_EHIP, std::string("moments: ") + hipGetErrorString(e));
-    return LBFV_OK;
+    return moved(c, move_fields(c->hc, c->hc.cur, c->transfer, c->stream, F_MOMENTS, {rho, ux, uy}), "moments");
 }
 
 int lbfv_totals(lbfv_ctx *c, double out[3]) {
@@ -2371,34 +2441,6 @@ int batch_set_time_block(lbfv_batch *b, int32_t steps) {
     return st;
 }
 
-template <typename T, typename S>
-int batch_state_t(lbfv_batch *b, int ci, int which, const double *d0, const double *d1, const double *d2,
-                  double *dout) {
-    HostCase &h = b->cases[ci];
-    double ext[4];
-    current_ext(h, ext);
-    StepParams<T> P = make_params<T>(h, ext);
-    const int64_t n = (int64_t)h.nx * h.ny;
-    const int blocks = (int)std::min<int64_t>((n + 255) / 256, 8192);
-    switch (which) {
-    case 0: hipLaunchKernelGGL((init_eq_kernel<T, S>), dim3(blocks), dim3(256), 0, b->stream, P, b->parity, d0, d1, d2, 1.0 / h.c, h.ref()); break;
-    case 1: hipLaunchKernelGGL((set_f_kernel<T, S>), dim3(blocks), dim3(256), 0, b->stream, P, b->parity, d0, h.ref()); break;
-    case 2: hipLaunchKernelGGL((get_f_kernel<T, S>), dim3(blocks), dim3(256), 0, b->stream, P, b->parity, dout, h.ref()); break;
-    default: hipLaunchKernelGGL((moments_kernel<T, S>), dim3(blocks), dim3(256), 0, b->stream, P, b->parity, dout, dout + n, dout + 2 * n, h.ref(), h.c); break;
-    }
-    if (hipGetLastError() != hipSuccess) return b->fail(LBFV_EHIP, "batch state kernel launch failed");
-    return LBFV_OK;
-}
-
-int batch_state(lbfv_batch *b, int ci, int which, const double *d0, const double *d1, const double *d2, double *dout) {
-    switch (b->variant) {
-    case V_F64: return batch_state_t<double, double>(b, ci, which, d0, d1, d2, dout);
-    case V_F32: return batch_state_t<float, float>(b, ci, which, d0, d1, d2, dout);
-    case V_BF16: return batch_state_t<float, __bf16>(b, ci, which, d0, d1, d2, dout);
-    default: return batch_state_t<float, _Float16>(b, ci, which, d0, d1, d2, dout);
-    }
-}
-
 }  // namespace
 
 extern "C" {
@@ -2448,13 +2490,12 @@ int lbfv_batch_create(int32_t n, const lbfv_case *cs, const lbfv_velset *vel, co
         }
         b->variant = h.variant;
         double ext[4];
-        if (hipMalloc(&h.buf[0], h.buffer_bytes()) != hipSuccess || hipMalloc(&h.buf[1], h.buffer_bytes()) != hipSuccess) {
-            (void)hipGetLastError();
-            st = b->fail(LBFV_ENOMEM, "batch: cannot allocate case buffers");
+        const hipError_t e = allocate_buffers(h, b->stream);
+        if (e != hipSuccess) {
+            st = h.buf[0] ? b->fail(LBFV_EHIP, std::string("batch: ") + hipGetErrorString(e))
+                          : b->fail(LBFV_ENOMEM, "batch: cannot allocate case buffers");
             break;
         }
-        (void)hipMemset(h.buf[0], 0, h.buffer_bytes());
-        (void)hipMemset(h.buf[1], 0, h.buffer_bytes());
         if (upload_metrics(h, ext, b->stream) != hipSuccess) st = b->fail(LBFV_EHIP, "batch: metric upload failed");
     }
     for (auto &h : b->cases) b->bnd = b->bnd || has_boundary(h);
@@ -2476,6 +2517,7 @@ int lbfv_batch_destroy(lbfv_batch *b) {
     if (b->d_params) (void)hipFree(b->d_params);
     if (b->d_items) (void)hipFree(b->d_items);
     for (auto &p : b->patches) drop_patches(p);
+    b->transfer.release();
     delete b;
     return LBFV_OK;
 }
@@ -2705,80 +2747,34 @@ int lbfv_batch_info(const lbfv_batch *b, int64_t *cells, int32_t *items) {
 int lbfv_batch_init_equilibrium(lbfv_batch *b, int32_t ci, const double *rho, const double *ux, const double *uy) {
     if (!b) return LBFV_EINVAL;
     if (ci < 0 || ci >= (int)b->cases.size() || !rho || !ux || !uy) return b->fail(LBFV_EINVAL, "bad case or field");
-    HostCase &h = b->cases[ci];
-    const int64_t n = (int64_t)h.nx * h.ny;
-    double *d;
-    if (hipMalloc((void **)&d, 3 * n * 8) != hipSuccess) {
-        (void)hipGetLastError();
-        return b->fail(LBFV_ENOMEM, "staging");
-    }
-    hipError_t e = hipMemcpyAsync(d, rho, n * 8, hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(d + n, ux, n * 8, hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(d + 2 * n, uy, n * 8, hipMemcpyHostToDevice, b->stream);
-    int st = e == hipSuccess ? batch_state(b, ci, 0, d, d + n, d + 2 * n, nullptr) : LBFV_OK;
-    const hipError_t es = hipStreamSynchronize(b->stream);
-    if (e == hipSuccess) e = es;
-    (void)hipFree(d);
-    if (st) return st;
-    if (e != hipSuccess) return b->fail(LBFV_EHIP, hipGetErrorString(e));
-    return LBFV_OK;
+    const HostCase &h = b->cases[ci];
+    std::vector<double *> a;
+    for (const double *f : {rho, ux, uy}) add_components(a, f, 1, h);
+    return moved(b, move_fields(h, b->parity, b->transfer, b->stream, F_INIT_EQ, a), "batch init_equilibrium");
 }
 
 int lbfv_batch_set_f(lbfv_batch *b, int32_t ci, const double *f) {
     if (!b) return LBFV_EINVAL;
     if (ci < 0 || ci >= (int)b->cases.size() || !f) return b->fail(LBFV_EINVAL, "bad case or array");
-    HostCase &h = b->cases[ci];
-    const int64_t n = (int64_t)h.nx * h.ny;
-    double *d;
-    if (hipMalloc((void **)&d, 9 * n * 8) != hipSuccess) {
-        (void)hipGetLastError();
-        return b->fail(LBFV_ENOMEM, "staging");
-    }
-    hipError_t e = hipMemcpyAsync(d, f, 9 * n * 8, hipMemcpyHostToDevice, b->stream);
-    int st = e == hipSuccess ? batch_state(b, ci, 1, d, nullptr, nullptr, nullptr) : LBFV_OK;
-    const hipError_t es = hipStreamSynchronize(b->stream);
-    if (e == hipSuccess) e = es;
-    (void)hipFree(d);
-    if (st) return st;
-    if (e != hipSuccess) return b->fail(LBFV_EHIP, hipGetErrorString(e));
-    return LBFV_OK;
-}
-
-static int batch_fetch(lbfv_batch *b, int32_t ci, int which, double *out, int64_t count) {
-    double *d;
-    if (hipMalloc((void **)&d, count * 8) != hipSuccess) {
-        (void)hipGetLastError();
-        return b->fail(LBFV_ENOMEM, "staging");
-    }
-    int st = batch_state(b, ci, which, nullptr, nullptr, nullptr, d);
-    hipError_t e = hipSuccess;
-    if (!st) e = hipMemcpyAsync(out, d, count * 8, hipMemcpyDeviceToHost, b->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
-    (void)hipFree(d);
-    if (st) return st;
-    if (e != hipSuccess) return b->fail(LBFV_EHIP, hipGetErrorString(e));
-    return LBFV_OK;
+    const HostCase &h = b->cases[ci];
+    std::vector<double *> a;
+    add_components(a, f, 9, h);
+    return moved(b, move_fields(h, b->parity, b->transfer, b->stream, F_SET_F, a), "batch set_f");
 }
 
 int lbfv_batch_get_f(lbfv_batch *b, int32_t ci, double *f) {
     if (!b) return LBFV_EINVAL;
     if (ci < 0 || ci >= (int)b->cases.size() || !f) return b->fail(LBFV_EINVAL, "bad case or array");
     const HostCase &h = b->cases[ci];
-    return batch_fetch(b, ci, 2, f, 9 * (int64_t)h.nx * h.ny);
+    std::vector<double *> a;
+    add_components(a, f, 9, h);
+    return moved(b, move_fields(h, b->parity, b->transfer, b->stream, F_GET_F, a), "batch get_f");
 }
 
 int lbfv_batch_moments(lbfv_batch *b, int32_t ci, double *rho, double *ux, double *uy) {
     if (!b) return LBFV_EINVAL;
     if (ci < 0 || ci >= (int)b->cases.size() || !rho || !ux || !uy) return b->fail(LBFV_EINVAL, "bad case or output");
-    const HostCase &h = b->cases[ci];
-    const int64_t n = (int64_t)h.nx * h.ny;
-    std::vector<double> tmp(3 * n);
-    int st = batch_fetch(b, ci, 3, tmp.data(), 3 * n);
-    if (st) return st;
-    memcpy(rho, tmp.data(), n * 8);
-    memcpy(ux, tmp.data() + n, n * 8);
-    memcpy(uy, tmp.data() + 2 * n, n * 8);
-    return LBFV_OK;
+    return moved(b, move_fields(b->cases[ci], b->parity, b->transfer, b->stream, F_MOMENTS, {rho, ux, uy}), "batch moments");
 }
 
 int lbfv_batch_nonfinite(lbfv_batch *b, int32_t *count) {

@@ -271,7 +271,7 @@ class Context:
         _check(lib().lbfv_set_f(self.h, _p(f)), self.h)
 
     def get_f(self) -> np.ndarray:
-        f = np.zeros((9, self.ny, self.nx))
+        f = np.empty((9, self.ny, self.nx))
         _check(lib().lbfv_get_f(self.h, _p(f)), self.h)
         return f
 
@@ -310,7 +310,8 @@ class Context:
 
     # ------------------------------------------------------------------ observables
     def moments(self):
-        rho = np.zeros((self.ny, self.nx)); ux = np.zeros_like(rho); uy = np.zeros_like(rho)
+        # (every element is written; large np.empty arrays come in huge pages, np.zeros arrays do not)
+        rho, ux, uy = (np.empty((self.ny, self.nx)) for _ in range(3))
         _check(lib().lbfv_moments(self.h, _p(rho), _p(ux), _p(uy)), self.h)
         return rho, ux, uy
 
@@ -420,7 +421,7 @@ class Batch:
 
     def get_f(self, i) -> np.ndarray:
         ny, nx = self.shapes[i]
-        f = np.zeros((9, ny, nx))
+        f = np.empty((9, ny, nx))
         _check(lib().lbfv_batch_get_f(self.h, int(i), _p(f)), self.h, batch=True)
         return f
 
@@ -429,7 +430,7 @@ class Batch:
 
     def moments(self, i):
         ny, nx = self.shapes[i]
-        rho = np.zeros((ny, nx)); ux = np.zeros_like(rho); uy = np.zeros_like(rho)
+        rho, ux, uy = (np.empty((ny, nx)) for _ in range(3))
         _check(lib().lbfv_batch_moments(self.h, int(i), _p(rho), _p(ux), _p(uy)), self.h, batch=True)
         return rho, ux, uy
 
