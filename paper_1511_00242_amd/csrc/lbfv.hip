@@ -220,6 +220,7 @@ struct lbfv_ctx {
     int64_t steps = 0, steps_at_check = 0;
     int rows = 0, wpb = 4;           // rows 0: not set, default_rows decides
     int pairs = 0;                   // two steps per launch, periodic mesh: a pair of waves per item
+    int cus = 0;                     // compute units of the device (0: not asked yet)
     int rows_of[2][5][2] = {};       // default_rows of the BKG / other kernels, time block and pairs (0: not asked yet)
     bool pinned = false;             // a program may hold captured work on the state's layout: keep it
     // graphs of `gsteps` launches, per scheme (+4 per further step per launch) and starting buffer
@@ -480,6 +481,8 @@ void free_case(HostCase &h) {
 // ------------------------------------------------------------------ kernel dispatch
 struct StepShape {
     int rows, wpb, nstrips, nwork, nblocks;
+    int side_rows = 0;        // pairs with x sides: rows of the row blocks of the strips at the sides,
+    uint32_t side_step = 0;   // and their share of the items in 2^-32, rounded up (0: as the others)
 };
 StepShape step_shape(const HostCase &h, int rows, int wpb) {
     StepShape s;
@@ -489,6 +492,33 @@ StepShape step_shape(const HostCase &h, int rows, int wpb) {
     s.nwork = s.nstrips * ((h.ny + rows - 1) / rows);
     s.nblocks = (s.nwork + wpb - 1) / wpb;
     return s;
+}
+
+// Shorter row blocks for the strips at the x sides of a mesh that a pair of waves per item
+// advances.  A row takes longer there (ghost cells, wall faces), and where all items run at once
+// those strips set the time of the launch.  With blocks of 1 / 1.3 of the rows, those that fill and
+// drain the levels included, they end with the others; us per step with blocks of 1, 1 / 1.15,
+// 1 / 1.3 and 1 / 1.6: 1024^2 cavity, 19 rows, FP64 DUGKS 25.0, 23.7, 23.2, 23.2, BKG 23.4, 22.4,
+// 21.9, 21.9, FP32 20.4, 18.8, 18.1, 18.1; 1200^2, 26 rows, FP64 DUGKS 31.4, 28.9, 28.2, 28.3.
+int side_block_rows(int rows) { return std::max(1, (rows + 4) * 10 / 13 - 4); }
+// work items with the sides' row blocks of `side_rows`
+int64_t items_with_sides(const HostCase &h, int nstrips, int rows, int side_rows) {
+    return (int64_t)(nstrips - 2) * ((h.ny + rows - 1) / rows) + 2 * (int64_t)((h.ny + side_rows - 1) / side_rows);
+}
+bool has_side_strips(const HostCase &h, int nstrips) { return !h.periodic_x() && nstrips >= 3; }
+// They go only as far as the additional items leave the items per SIMD what they were (a pair puts
+// a wave on two of a CU's four SIMDs).
+void balance_sides(const HostCase &h, int cus, StepShape &s) {
+    if (!has_side_strips(h, s.nstrips) || cus <= 0) return;
+    const int64_t quantum = 2 * cus, loads = (s.nwork + quantum - 1) / quantum;
+    for (int rows = side_block_rows(s.rows); rows < s.rows; ++rows) {
+        const int64_t n = items_with_sides(h, s.nstrips, s.rows, rows);
+        if ((n + quantum - 1) / quantum > loads) continue;
+        s.side_rows = rows;
+        s.side_step = (uint32_t)((2ull * (uint64_t)((h.ny + rows - 1) / rows) * (1ull << 32) + n - 1) / n);
+        s.nwork = (int)n;
+        return;
+    }
 }
 
 // Kernels of a mesh with a non-periodic side read their parameters through a device copy
@@ -740,15 +770,19 @@ struct StepArgs {
     StepParams<float> pf;
     const void *pptr = nullptr;   // device copy of the parameters, for kernels that take a pointer
     int parity, rows, nstrips, nwork;
+    int side_rows;
+    uint32_t side_step;
     int steps;                    // patch form: steps of the launch and the patches
     PatchGrid grid;
-    void *args[5];
+    void *args[7];
     void bind(bool f64) {
         args[0] = f64 ? (void *)&pd : (void *)&pf;
         args[1] = &parity;
         args[2] = &rows;
         args[3] = &nstrips;
         args[4] = &nwork;
+        args[5] = &side_rows;
+        args[6] = &side_step;
     }
     void bind_patch(const PatchGrid &g, int n) {
         grid = g;
@@ -766,6 +800,8 @@ void fill_args(const HostCase &h, const double ext[4], const StepShape &sh, int 
     a.rows = sh.rows;
     a.nstrips = sh.nstrips;
     a.nwork = sh.nwork;
+    a.side_rows = sh.side_rows;
+    a.side_step = sh.side_step;
     a.bind(is_f64(h.variant));
 }
 
@@ -783,14 +819,17 @@ int resident_waves(void *fn, int wpb) {
 
 // Row-block heights whose wave count fills the resident slots in k whole rounds:
 // few prologue rows re-read and no partial last round (strip: output columns per wave).
-std::vector<int> balanced_rows(const HostCase &h, int slots, int strip, int kmax = 4) {
+// sides: room for the row blocks that balance_sides makes.
+std::vector<int> balanced_rows(const HostCase &h, int slots, int strip, int kmax = 4, bool sides = false) {
     std::vector<int> out;
     if (slots <= 0) return out;
     const int nstrips = (h.nx + strip - 1) / strip;
     for (int k = 1; k <= kmax; ++k) {
         const int blocks = (k * slots) / nstrips;   // row blocks per strip
         if (blocks < 1) continue;
-        const int r = (h.ny + blocks - 1) / blocks;
+        int r = (h.ny + blocks - 1) / blocks;
+        if (sides && has_side_strips(h, nstrips))
+            while (r < h.ny && items_with_sides(h, nstrips, r, side_block_rows(r)) > (int64_t)k * slots) ++r;
         if (r >= 4 && r <= h.ny) out.push_back(r);
     }
     return out;
@@ -815,7 +854,10 @@ int default_rows(const HostCase &h, int scheme, int wpb, int tb = 1, bool pairs 
         for (int k = 1; k <= 8; ++k) {
             const int blocks = std::min(k * slots / nstrips, h.ny);
             if (blocks < 1) continue;
-            const int rows = (h.ny + blocks - 1) / blocks, cost = k * (rows + 3 * tb);
+            int rows = (h.ny + blocks - 1) / blocks;
+            if (pairs && has_side_strips(h, nstrips))   // room for balance_sides
+                while (rows < h.ny && items_with_sides(h, nstrips, rows, side_block_rows(rows)) > (int64_t)k * slots) ++rows;
+            const int cost = k * (rows + 3 * tb);
             if (!best || cost < least) {
                 best = rows;
                 least = cost;
@@ -1005,6 +1047,22 @@ int march_rows(lbfv_ctx *c, int scheme, int tb) {
     return rows;
 }
 
+int device_cus(lbfv_ctx *c) {
+    int dev = 0;
+    if (!c->cus && (hipGetDevice(&dev) != hipSuccess ||
+                    hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)) {
+        (void)hipGetLastError();
+        c->cus = 0;
+    }
+    return c->cus;
+}
+// the shape of a march of tb steps per launch
+StepShape march_shape(lbfv_ctx *c, int scheme, int tb) {
+    StepShape sh = step_shape(c->hc, march_rows(c, scheme, tb), c->wpb);
+    if (paired(c, tb) && !c->hc.periodic_x()) balance_sides(c->hc, device_cus(c), sh);
+    return sh;
+}
+
 // the step kernel of a launch of tb steps: a chain of tb waves per work item (tb = 3, 4;
 // doubly periodic meshes), two steps (in a strip layout of 60 columns or fewer; with or
 // without non-periodic sides; one wave or a pair of waves per work item), or one
@@ -1103,8 +1161,7 @@ int launch_patch(lbfv_ctx *c, int scheme, int parity, const double ext[4], int s
 }
 
 int launch_one(lbfv_ctx *c, int scheme, int parity, const double ext[4], int tb = 1) {
-    HostCase &h = c->hc;
-    StepShape sh = step_shape(h, march_rows(c, scheme, tb), c->wpb);
+    StepShape sh = march_shape(c, scheme, tb);
     StepArgs a;
     int st = launch_args(c, scheme, parity, ext, sh, a);
     if (st) return st;
@@ -1117,7 +1174,7 @@ int launch_one(lbfv_ctx *c, int scheme, int parity, const double ext[4], int tb 
 // a graph of gsteps launches of tb steps each, in the patch form or as marches
 int build_graph(lbfv_ctx *c, int scheme, int parity0, const double ext[4], int tb, bool patch) {
     HostCase &h = c->hc;
-    StepShape sh = step_shape(h, patch ? 1 : march_rows(c, scheme, tb), c->wpb);
+    const StepShape sh = patch ? step_shape(h, 1, 1) : march_shape(c, scheme, tb);
     hipGraph_t g;
     HIPCHK(hipGraphCreate(&g, 0));
     hipGraphNode_t prev = nullptr;
@@ -2040,6 +2097,9 @@ extern "C" int lbfv_autotune(lbfv_ctx *c, int scheme, int32_t trial_steps, const
     for (int r : balanced_rows(h, resident_waves(step2p_fn_variant(h.variant, scheme, has_boundary(h), ref_terms(h)), 2) / 2,
                                STRIP2, 8))
         cands.push_back({2, 1, r, 1});
+    // with x sides: whole rounds of the SIMDs, whose loads the shorter row blocks there even out
+    if (const int cus = has_side_strips(h, (h.nx + STRIP2 - 1) / STRIP2) ? device_cus(c) : 0)
+        for (int r : balanced_rows(h, 2 * cus, STRIP2, 8, true)) cands.push_back({2, 1, r, 1});
     // three and four steps per launch on doubly periodic meshes: a chain of waves per item
     // (one workgroup each); the balanced heights count resident chains
     if (!has_boundary(h))
