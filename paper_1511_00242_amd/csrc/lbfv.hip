@@ -841,7 +841,7 @@ std::vector<int> balanced_rows(const HostCase &h, int slots, int strip, int kmax
 // each item's own and the 3 tb that fill and drain its levels.  That is the autotuner's choice to
 // within a few rows (4096^2 FP64 DUGKS, chains of four: 205 rows; 1024^2: 40; 512^2: 11), where
 // the one-step heights of 8 and 16 rows ran a chain of four on 1536^2 FP16 at 35.2 us a step
-// against 24.0.
+// against 28.5.
 int default_rows(const HostCase &h, int scheme, int wpb, int tb = 1, bool pairs = false) {
     const int64_t cells = (int64_t)h.nx * h.ny;
     const bool bnd = !(h.periodic_x() && h.periodic_y()), ref = ref_terms(h);
@@ -1364,13 +1364,15 @@ struct Advance {
 // periodic mesh, a pair of waves with sides.
 int unasked_time_block(const HostCase &h) { return !has_boundary(h) && std::min(h.nx, h.ny) >= 8 ? 4 : 2; }
 // Where no shape was set, meshes up to this size take patches in calls of any length, larger ones
-// in long calls the marches above: the two pass each other near 450^2 cells in FP64 (vortex, DUGKS:
-// 448^2 patches 8.4 us a step, chains 7.1; 384^2 5.6 and 6.4) and 600^2 in FP32 (512^2 5.6 and 7.2;
-// 640^2 10.7 and 8.6), with sides a little above that (cavity FP64 448^2 9.7 and 10.3, 512^2 12.9
-// and 11.1; FP32 640^2 10.6 and 10.9, 768^2 14.3 and 12.6).
-int64_t patch_cells(const HostCase &h) {
+// in long calls the marches above.  us a step, patches and marches: periodic, DUGKS FP64 384^2 5.6
+// and 6.4, 448^2 8.4 and 7.1; FP32 512^2 5.6 and 7.2, 640^2 10.7 and 8.6.  With sides the pairs
+// gain more on DUGKS than on BKG: cavity FP64 DUGKS 384^2 6.8 and 7.6, 416^2 8.0 and 7.8, 512^2
+// 12.9 and 9.8, BKG 448^2 6.7 and 7.2, 512^2 8.1 and 8.3; FP32 DUGKS 576^2 8.4 and 9.1, 608^2 9.5
+// and 9.0, BKG 672^2 7.8 and 8.8, 736^2 9.1 and 9.1.
+int64_t patch_cells(const HostCase &h, int scheme) {
     const bool f64 = is_f64(h.variant);
-    return has_boundary(h) ? (f64 ? 1 << 18 : 1 << 19) : (f64 ? 170000 : 350000);
+    if (has_boundary(h) && scheme == SCHEME_BKG) return f64 ? 1 << 18 : 1 << 19;
+    return f64 ? 170000 : (has_boundary(h) ? 360000 : 350000);
 }
 constexpr int LONG_CALL = 16;   // steps from which moving the state to another layout pays
 int plan_advance(lbfv_ctx *c, int scheme, int n, Advance &a) {
@@ -1388,7 +1390,7 @@ int plan_advance(lbfv_ctx *c, int scheme, int n, Advance &a) {
     }
     // 16-bit storage is rounded after every step unless several per launch were asked for
     const bool wide = h.variant == V_F64 || h.variant == V_F32;
-    if (c->form == FORM_AUTO && wide && cells > patch_cells(h)) {
+    if (c->form == FORM_AUTO && wide && cells > patch_cells(h, scheme)) {
         const int tb = unasked_time_block(h), strip = SLOTS - 2 * tb;
         if (h.strip == strip || (n >= LONG_CALL && !c->pinned)) {
             a.per = tb;
@@ -1397,7 +1399,7 @@ int plan_advance(lbfv_ctx *c, int scheme, int n, Advance &a) {
     }
     // (short calls on larger meshes: patches too, but for FP64 with sides, whose few resident
     // waves gain nothing there: 1024^2 cavity, three steps of DUGKS, 70 us a step against 68)
-    const int64_t most = has_boundary(h) && h.variant == V_F64 ? patch_cells(h) : PATCH_CELLS;
+    const int64_t most = has_boundary(h) && h.variant == V_F64 ? 1 << 18 : PATCH_CELLS;
     if (c->form == FORM_PATCH || cells <= most) {
         const PatchPlan &p = patch_plan(c, scheme);
         a.patch = p.waves > 0;
