@@ -130,7 +130,9 @@ int lbfv_set_symmetry(lbfv_ctx *ctx, int side);
  * its leading edge): cells first_cell..nx-1 of the side are a half-way bounce-back wall
  * moving with (uwx, uwy); the cells before it keep the side's kind, which must already be
  * set and not periodic (else EINVAL).  Setting the side's kind again removes the segment.
- * EINVAL also for an x-side, first_cell outside [0, nx) or a non-finite velocity. */
+ * EINVAL also for an x-side, first_cell outside [0, nx) or a non-finite velocity.
+ * On a mesh that is periodic in x the segment ends at the seam, and every launch advances one
+ * step, whatever lbfv_set_time_block asks for. */
 int lbfv_set_wall_from(lbfv_ctx *ctx, int side, int32_t first_cell, double uwx, double uwy);
 
 /* State.  f~ of an equilibrium state is feq (Omega(feq) = 0). */

@@ -637,6 +637,14 @@ bool has_boundary(const HostCase &h) { return !(h.periodic_x() && h.periodic_y()
 // the FP32 step kernels with the reference-velocity terms: only while a reference velocity is set
 bool ref_terms(const HostCase &h) { return !is_f64(h.variant) && (h.u0[0] != 0.0 || h.u0[1] != 0.0); }
 
+// A wall segment on a mesh that is periodic in x ends at the seam, and the two cells that meet there
+// see each other's ghost row differently: to cell 0 the column west of it lies ahead of the segment,
+// to cell nx - 1 the column east of it lies in the segment, while each takes its own rule for itself.
+// A launch of one step evaluates the seam once for each of them, in the outer lanes of two strips.
+// One of several steps would need both values of either cell at every level, so such a mesh
+// advances one step per launch, whatever shape is set.
+bool one_step_only(const HostCase &h) { return h.periodic_x() && (h.wfrom[SIDE_S] >= 0 || h.wfrom[SIDE_N] >= 0); }
+
 // ------------------------------------------------------------------ patches
 // Widest extent, ghost and halo cells included, of `parts` patches along an axis of n cells.
 // Patches within a halo of a non-periodic side are cut off by it (at most 9 of them per end),
@@ -688,6 +696,7 @@ bool plan_patch(const HostCase &h, int per_wave, int waves, int halo, PatchPlan 
     p.per_wave = per_wave;
     p.max_waves = waves;
     if (h.plane * (int64_t)h.esize >= (1ll << 31)) return false;   // 32-bit offsets within a plane
+    if (one_step_only(h)) return false;
     if ((h.periodic_x() && h.nx <= halo) || (h.periodic_y() && h.ny <= halo)) return false;   // the halo wraps once
     g.npx = patch_parts(h.nx, h.periodic_x(), halo, 64 / per_wave);
     g.npy = g.npx ? patch_parts(h.ny, h.periodic_y(), halo, waves * per_wave) : 0;
@@ -1380,7 +1389,7 @@ int plan_advance(lbfv_ctx *c, int scheme, int n, Advance &a) {
     const int64_t cells = (int64_t)h.nx * h.ny;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) (void)hipGetLastError();
-    a.per = h.tblock;
+    if (!one_step_only(h)) a.per = h.tblock;
     if (c->form == FORM_MARCH) return LBFV_OK;
     a.exact = true;
     // a stream under capture gets one-step launches
@@ -1390,7 +1399,7 @@ int plan_advance(lbfv_ctx *c, int scheme, int n, Advance &a) {
     }
     // 16-bit storage is rounded after every step unless several per launch were asked for
     const bool wide = h.variant == V_F64 || h.variant == V_F32;
-    if (c->form == FORM_AUTO && wide && cells > patch_cells(h, scheme)) {
+    if (c->form == FORM_AUTO && wide && cells > patch_cells(h, scheme) && !one_step_only(h)) {
         const int tb = unasked_time_block(h), strip = SLOTS - 2 * tb;
         if (h.strip == strip || (n >= LONG_CALL && !c->pinned)) {
             a.per = tb;
@@ -2112,6 +2121,9 @@ extern "C" int lbfv_autotune(lbfv_ctx *c, int scheme, int32_t trial_steps, const
             void *fn = stepc_fn_variant(h.variant, scheme, t, ref_terms(h));
             for (int r : balanced_rows(h, resident_waves(fn, t) / t, SLOTS - 2 * t, 8)) cands.push_back({t, 0, r, 1});
         }
+    if (one_step_only(h))
+        cands.erase(std::remove_if(cands.begin(), cands.end(), [](const std::array<int, 4> &k) { return k[0] > 1; }),
+                    cands.end());
     std::sort(cands.begin(), cands.end());
     cands.erase(std::unique(cands.begin(), cands.end()), cands.end());
     // one trial of the shape set on the context: ms per step
