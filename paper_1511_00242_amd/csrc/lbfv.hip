@@ -2457,18 +2457,25 @@ int batch_launch_patches(lbfv_batch *b, int scheme, int parity, int steps) {
     return LBFV_OK;
 }
 
-// a graph of gsteps launches of the current time block, or of the patch form
+// Launches of a graph.  In the patch form an even number, whatever length was set: the state then
+// comes back to the buffer it was in, as after the even number of steps that one-step launches
+// would have taken (a program may replay captured work that names that buffer).
+int64_t graph_launches(const lbfv_batch *b, bool patch) {
+    return patch ? (int64_t)b->gsteps + (b->gsteps & 1) : b->gsteps;
+}
+
+// a graph of launches of the current time block, or of the patch form
 int batch_build_graph(lbfv_batch *b, int scheme, int parity0, bool patch) {
     const bool two = b->tblock == 2;
     hipGraph_t g;
     if (hipGraphCreate(&g, 0) != hipSuccess) return b->fail(LBFV_EHIP, "hipGraphCreate failed");
     hipGraphNode_t prev = nullptr;
-    for (int s = 0; s < b->gsteps; ++s) {
-        BatchArgs a{b->d_params, b->d_items, b->nitems, (parity0 + s) & 1};
+    for (int64_t s = 0; s < graph_launches(b, patch); ++s) {
+        BatchArgs a{b->d_params, b->d_items, b->nitems, (int)((parity0 + s) & 1)};
         a.bind();
         hipKernelNodeParams kp;
         memset(&kp, 0, sizeof(kp));
-        PatchArgs pa(b, scheme, (parity0 + s) & 1, b->patches[scheme].halo);
+        PatchArgs pa(b, scheme, (int)((parity0 + s) & 1), b->patches[scheme].halo);
         if (patch) {
             kp.func = batch_patch_fn_variant(b->variant, scheme, b->bnd);
             kp.gridDim = dim3(b->patches[scheme].count);
@@ -2899,7 +2906,8 @@ int lbfv_batch_step(lbfv_batch *b, int scheme, int32_t n) {
     // one-step launch on the same layout.  The patch form takes up to its halo width.
     const bool two = b->tblock == 2;
     const int per = patch ? b->patches[scheme].halo : (two ? 2 : 1);
-    while (n >= per * b->gsteps) {
+    const int64_t replay = graph_launches(b, patch);
+    while (n >= per * replay) {
         hipGraphExec_t &g = b->gexec[scheme + (patch ? 2 : 0)][b->parity];
         if (!g) {
             st = batch_build_graph(b, scheme, b->parity, patch);
@@ -2907,8 +2915,8 @@ int lbfv_batch_step(lbfv_batch *b, int scheme, int32_t n) {
         }
         hipError_t e = hipGraphLaunch(g, b->stream);
         if (e != hipSuccess) return b->fail(LBFV_EHIP, std::string("hipGraphLaunch: ") + hipGetErrorString(e));
-        b->parity ^= (b->gsteps & 1);
-        n -= per * b->gsteps;
+        b->parity ^= (int)(replay & 1);
+        n -= (int32_t)(per * replay);
     }
     // (patches: an even or odd number of launches as the steps are, like one-step launches)
     int launches = (n + per - 1) / per;
