@@ -11,6 +11,7 @@ SRC = os.path.join(PKG, "csrc", "lbfv.hip")
 LIB = os.path.join(PKG, "liblbfv.so")
 DEPS = [SRC, os.path.join(PKG, "csrc", "kernels.hpp"), os.path.join(PKG, "csrc", "aux_kernels.hpp"),
         os.path.join(PKG, "csrc", "batch_kernels.hpp"), os.path.join(PKG, "csrc", "patch_kernels.hpp"),
+        os.path.join(PKG, "csrc", "schedule.hpp"),
         os.path.join(ROOT, "include", "lbfv.h")]
 
 HIPCC_FLAGS = [

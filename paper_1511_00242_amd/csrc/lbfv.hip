@@ -5,6 +5,7 @@
 #include "aux_kernels.hpp"
 #include "batch_kernels.hpp"
 #include "patch_kernels.hpp"
+#include "schedule.hpp"
 
 #include <algorithm>
 #include <type_traits>
@@ -1489,10 +1490,8 @@ int do_steps(lbfv_ctx *c, int scheme, int32_t n) {
         // The steps left over: launches of `per` steps and one of fewer, in the same strip layout
         // (every narrower march fits a wider halo's strip); or an even or odd number of launches
         // as the steps are, none of them shorter than need be.
-        int launches = (left + per - 1) / per;
-        if (adv.exact) launches += (launches ^ left) & 1;
-        for (; launches > 0; --launches) {
-            const int k = adv.exact ? (left + launches - 1) / launches : std::min(per, left);
+        for (int launches = tail_launches(left, per, adv.exact); launches > 0; --launches) {
+            const int k = launch_steps(left, launches, per, adv.exact);
             if ((st = launch(k))) return st;
             left -= k;
         }
@@ -2126,19 +2125,19 @@ extern "C" int lbfv_autotune(lbfv_ctx *c, int scheme, int32_t trial_steps, const
                     cands.end());
     std::sort(cands.begin(), cands.end());
     cands.erase(std::unique(cands.begin(), cands.end()), cands.end());
-    // one trial of the shape set on the context: ms per step
-    auto trial = [&](double &per) {
+    // one trial of the shape set on the context, `steps` of them timed: ms per step
+    auto trial = [&](int steps, double &per) {
         drop_graphs(c);
         int ts = do_steps(c, scheme, 2);   // warm-up
         if (ts) return ts;
         hipError_t he = hipEventRecord(e0, c->stream);
-        if (he == hipSuccess && (ts = do_steps(c, scheme, trial_steps))) return ts;
+        if (he == hipSuccess && (ts = do_steps(c, scheme, steps))) return ts;
         float t = 0;
         if (he == hipSuccess) he = hipEventRecord(e1, c->stream);
         if (he == hipSuccess) he = hipEventSynchronize(e1);
         if (he == hipSuccess) he = hipEventElapsedTime(&t, e0, e1);
         if (he != hipSuccess) return c->fail(LBFV_EHIP, std::string("autotune timing: ") + hipGetErrorString(he));
-        per = t / trial_steps;
+        per = t / steps;
         return (int)LBFV_OK;
     };
     c->form = FORM_MARCH;
@@ -2148,7 +2147,7 @@ extern "C" int lbfv_autotune(lbfv_ctx *c, int scheme, int32_t trial_steps, const
         c->rows = cand[2];
         c->wpb = cand[3];
         double per;
-        if ((st = trial(per))) break;
+        if ((st = trial(trial_steps, per))) break;
         if (per < best) {
             best = per;
             best_t = cand[0];
@@ -2174,7 +2173,7 @@ extern "C" int lbfv_autotune(lbfv_ctx *c, int scheme, int32_t trial_steps, const
             if (!p.waves || p.cost > limit) continue;
             c->plan[scheme == SCHEME_BKG] = p;
             double per;
-            if ((st = trial(per))) break;
+            if ((st = trial(trial_length(halo, trial_steps), per))) break;
             if (per < best) {
                 best = per;
                 best_plan = p;
@@ -2919,10 +2918,8 @@ int lbfv_batch_step(lbfv_batch *b, int scheme, int32_t n) {
         n -= (int32_t)(per * replay);
     }
     // (patches: an even or odd number of launches as the steps are, like one-step launches)
-    int launches = (n + per - 1) / per;
-    if (patch) launches += (launches ^ n) & 1;
-    for (; launches > 0; --launches) {
-        const int k = patch ? (n + launches - 1) / launches : std::min(n, per);
+    for (int launches = tail_launches(n, per, patch); launches > 0; --launches) {
+        const int k = launch_steps(n, launches, per, patch);
         st = patch ? batch_launch_patches(b, scheme, b->parity, k) : batch_launch_one(b, scheme, b->parity, k == 2);
         if (st) return st;
         b->parity ^= 1;
