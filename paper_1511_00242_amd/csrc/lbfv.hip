@@ -1391,13 +1391,16 @@ int plan_advance(lbfv_ctx *c, int scheme, int n, Advance &a) {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) (void)hipGetLastError();
     if (!one_step_only(h)) a.per = h.tblock;
-    if (c->form == FORM_MARCH) return LBFV_OK;
+    const bool capturing = capture != hipStreamCaptureStatusNone;
+    if (capturing) c->pinned = true;
+    if (c->form == FORM_MARCH) {
+        // (a shape that was set after a call had moved the state to another layout; one-step
+        // marches run in every layout)
+        return c->pinned ? (int)LBFV_OK : set_layout(c, SLOTS - 2 * h.tblock);
+    }
     a.exact = true;
     // a stream under capture gets one-step launches
-    if (capture != hipStreamCaptureStatusNone) {
-        c->pinned = true;
-        return LBFV_OK;
-    }
+    if (capturing) return LBFV_OK;
     // 16-bit storage is rounded after every step unless several per launch were asked for
     const bool wide = h.variant == V_F64 || h.variant == V_F32;
     if (c->form == FORM_AUTO && wide && cells > patch_cells(h, scheme) && !one_step_only(h)) {
@@ -1433,10 +1436,10 @@ int set_time_block(lbfv_ctx *c, int32_t steps) {
     return LBFV_OK;
 }
 
-// A march control was set: marches in the layout of the time block from here on.
+// A march control was set: marches from here on (the next call moves the state to their layout).
 int take_marches(lbfv_ctx *c) {
     c->form = FORM_MARCH;
-    return set_layout(c, SLOTS - 2 * c->hc.tblock);
+    return LBFV_OK;
 }
 
 int do_steps(lbfv_ctx *c, int scheme, int32_t n) {

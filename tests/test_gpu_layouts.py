@@ -1,0 +1,88 @@
+"""When a context moves its state to another strip layout: launches that a program captured, and
+buffers that it owns, go on naming the state; and a shape that is set is the one that runs."""
+import numpy as np
+import pytest
+
+from paper_1511_00242_amd import inputs as I
+from paper_1511_00242_amd import lbfv as L
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need an MI355X"
+    torch.cuda.set_device(0)
+    yield
+
+
+def captured_totals(ctx, s):
+    import torch
+    out = torch.zeros(4, dtype=torch.float64, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        ctx.totals_device(out.data_ptr())
+
+    def replay():
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        return out.cpu().numpy()[:3].copy()
+    return replay
+
+
+def set_rows(ctx):
+    ctx.set_tile(24, 4)
+
+
+def set_pairs(ctx):
+    ctx.set_wave_pairs(True)
+
+
+# chains of four (56 columns) and pairs (60 columns) unasked
+@pytest.mark.parametrize("sides", [False, True])
+@pytest.mark.parametrize("shape", [set_rows, set_pairs])
+def test_captured_totals_after_a_long_call_and_a_shape(sides, shape):
+    import torch
+    w = I.cavity(520, stretched=False) if sides else I.taylor_green(450)
+    s = torch.cuda.Stream()
+    with L.Context(w.xf, w.yf, w.tau, w.dt, bcs=w.bcs, check_every=0, stream=s.cuda_stream) as ctx:
+        ctx.init_equilibrium(w.rho, w.ux * 30, w.uy * 30 + 0.01)
+        ctx.dugks_step(40)
+        totals = captured_totals(ctx, s)
+        for k in (2, 64, 100):
+            ctx.dugks_step(k)
+            assert np.array_equal(totals(), ctx.totals()), k
+            if k == 2:
+                shape(ctx)
+                assert np.array_equal(totals(), ctx.totals())
+
+
+def test_captured_steps_after_a_shape_on_a_moved_layout():
+    """A shape set after a long call, then steps captured, then long calls again."""
+    import torch
+    w = I.taylor_green(450)
+    s = torch.cuda.Stream()
+    outs = []
+    for captured in (True, False):
+        with L.Context(w.xf, w.yf, w.tau, w.dt, bcs=w.bcs, check_every=0, stream=s.cuda_stream) as ctx:
+            ctx.init_equilibrium(w.rho, w.ux, w.uy)
+            if not captured:
+                ctx.set_tile(24, 4)
+                ctx.dugks_step(40 + 4 + 64 + 4)
+            else:
+                ctx.dugks_step(40)
+                ctx.set_tile(24, 4)
+                torch.cuda.synchronize()
+                g = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(g, stream=s):
+                    ctx.dugks_step(4)
+                g.replay()
+                torch.cuda.synchronize()
+                ctx.dugks_step(64)
+                torch.cuda.synchronize()
+                g.replay()
+                torch.cuda.synchronize()
+            outs.append(ctx.get_f())
+    assert np.array_equal(outs[0], outs[1])
