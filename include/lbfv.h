@@ -146,7 +146,10 @@ int lbfv_set_f(lbfv_ctx *ctx, const double *f);   /* f~, [9][ny][nx] FP64 */
 int lbfv_get_f(lbfv_ctx *ctx, double *f);         /* f~, [9][ny][nx] FP64 */
 /* Use caller-owned device buffers (e.g. PyTorch tensors) for the two state buffers;
  * each must hold lbfv_required_bytes and outlive the context.  The current state is
- * not carried over (set it again afterwards). */
+ * not carried over (set it again afterwards).  The layout of what they hold changes only in
+ * lbfv_set_time_block, lbfv_autotune and, from 3 or 4 steps per launch, the first step call after a
+ * side stopped being periodic; between such calls a program may save and restore the state by copying
+ * both buffers, an even number of steps apart. */
 int lbfv_bind_buffers(lbfv_ctx *ctx, void *dev_a, void *dev_b, size_t bytes);
 int lbfv_required_bytes(const lbfv_ctx *ctx, size_t *bytes_per_buffer);
 

@@ -223,7 +223,8 @@ struct lbfv_ctx {
     int pairs = 0;                   // two steps per launch, periodic mesh: a pair of waves per item
     int cus = 0;                     // compute units of the device (0: not asked yet)
     int rows_of[2][5][2] = {};       // default_rows of the BKG / other kernels, time block and pairs (0: not asked yet)
-    bool pinned = false;             // a program may hold captured work on the state's layout: keep it
+    bool pinned = false;             // a program may hold captured work on the state's layout, or owns the
+                                     // buffers: keep it
     // graphs of `gsteps` launches, per scheme (+4 per further step per launch) and starting buffer
     int gsteps = 32;
     // (16 + scheme: the patch form)
@@ -1748,6 +1749,9 @@ int lbfv_bind_buffers(lbfv_ctx *c, void *a, void *b, size_t bytes) {
     h.buf[1] = b;
     h.own = false;
     h.cur = 0;
+    // the layout of the time block, for good: the program may save and restore what the buffers hold
+    h.set_strip(SLOTS - 2 * h.tblock);
+    c->pinned = true;
     c->has_state = false;
     drop_graphs(c);
     HIPCHK(hipMemsetAsync(a, 0, h.buffer_bytes(), c->stream));

@@ -86,3 +86,27 @@ def test_captured_steps_after_a_shape_on_a_moved_layout():
                 torch.cuda.synchronize()
             outs.append(ctx.get_f())
     assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("sides", [False, True])
+def test_bound_buffers_can_be_saved_and_restored(sides):
+    """A program that owns the two buffers saves the state by copying them and puts it back after
+    an even number of steps; no call that it makes asks for another layout."""
+    import torch
+    w = I.cavity(520, stretched=False) if sides else I.taylor_green(450)
+    with L.Context(w.xf, w.yf, w.tau, w.dt, bcs=w.bcs) as ctx:
+        a, b = ctx.bind_torch_buffers()
+        ctx.init_equilibrium(w.rho, w.ux, w.uy)
+        ctx.dugks_step(4)
+        f0 = ctx.get_f()
+        torch.cuda.synchronize()
+        kept = a.clone(), b.clone()
+        ctx.dugks_step(40)
+        f1 = ctx.get_f()
+        torch.cuda.synchronize()
+        a.copy_(kept[0])
+        b.copy_(kept[1])
+        torch.cuda.synchronize()
+        assert np.array_equal(ctx.get_f(), f0)
+        ctx.dugks_step(40)
+        assert np.array_equal(ctx.get_f(), f1)
