@@ -1438,8 +1438,10 @@ int set_time_block(lbfv_ctx *c, int32_t steps) {
 }
 
 // A march control was set: marches from here on (the next call moves the state to their layout).
+// Graphs built without a shape may hold other kernels and row heights for the same time block.
 int take_marches(lbfv_ctx *c) {
     c->form = FORM_MARCH;
+    drop_graphs(c);
     return LBFV_OK;
 }
 
@@ -1889,8 +1891,7 @@ int lbfv_residual(lbfv_ctx *c, double *r) {
 int lbfv_set_time_block(lbfv_ctx *c, int32_t steps) {
     if (!c) return LBFV_EINVAL;
     int st = set_time_block(c, steps);
-    if (!st) c->form = FORM_MARCH;
-    return st;
+    return st ? st : take_marches(c);
 }
 
 int lbfv_get_time_block(const lbfv_ctx *c, int32_t *steps) {
@@ -1946,7 +1947,6 @@ int lbfv_set_tile(lbfv_ctx *c, int32_t rows, int32_t wpb) {
     if (rows > 0) c->rows = rows;
     if (wpb > 0) c->wpb = wpb;
     memset(c->rows_of, 0, sizeof(c->rows_of));
-    drop_graphs(c);
     return rows > 0 || wpb > 0 ? take_marches(c) : (int)LBFV_OK;
 }
 
@@ -1962,7 +1962,6 @@ int lbfv_set_wave_pairs(lbfv_ctx *c, int32_t on) {
     if (!c) return LBFV_EINVAL;
     if (on != 0 && on != 1) return c->fail(LBFV_EINVAL, "lbfv_set_wave_pairs: 0 or 1");
     c->pairs = on;
-    drop_graphs(c);
     return take_marches(c);
 }
 

@@ -110,3 +110,30 @@ def test_bound_buffers_can_be_saved_and_restored(sides):
         assert np.array_equal(ctx.get_f(), f0)
         ctx.dugks_step(40)
         assert np.array_equal(ctx.get_f(), f1)
+
+
+def kernels_of(call):
+    """Names of the kernels that a call runs, graph replays included."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    return {e.name for e in p.events()}
+
+
+def test_the_time_block_that_is_set_is_the_one_that_runs():
+    """After a long call in which a context with sides took pairs of waves by itself, two steps per
+    launch asked for without pairs run on one wave per item, in graph replays too."""
+    w = I.cavity(520, stretched=False)
+    with L.Context(w.xf, w.yf, w.tau, w.dt, bcs=w.bcs, check_every=0) as ctx:
+        ctx.init_equilibrium(w.rho, w.ux, w.uy)
+        unasked = kernels_of(lambda: ctx.dugks_step(128))
+        ctx.set_time_block(2)
+        assert not ctx.get_wave_pairs()
+        asked = kernels_of(lambda: ctx.dugks_step(128))
+    steps = lambda names: sorted(n for n in names if "step2b" in n)   # noqa: E731
+    print(unasked, asked, flush=True)
+    assert steps(unasked) and all("step2bp" in n for n in steps(unasked))
+    assert steps(asked) and not any("step2bp" in n for n in steps(asked))
