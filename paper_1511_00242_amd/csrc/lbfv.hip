@@ -117,15 +117,21 @@ public:
             if (e == hipSuccess && !up) copy(false, arrays, 0, cells, slot(0, total));
             return e;
         }
-        hipError_t e = reserve((size_t)std::min<int64_t>(2 * threads * chunk * width, total), 2 * threads);
+        hipError_t e = reserve((size_t)std::min<int64_t>(2 * threads * chunk * width, total), 2 * threads + 1);
         if (e != hipSuccess) return e;
         int dev = 0;
         if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+        // The handle hipStreamPerThread means another stream in each thread: what the other threads
+        // enqueue has to wait for what is queued on the caller's.
+        const bool own_streams = stream == hipStreamPerThread && threads > 1;
+        const hipEvent_t queued = events_[2 * threads];
+        if (own_streams && (e = hipEventRecord(queued, stream)) != hipSuccess) return e;
         std::vector<hipError_t> result(threads, hipSuccess);
         // thread t: chunks t, t + threads, ..., alternating between its two slots
         auto work = [&](int t, int stride) {
             hipError_t &r = result[t];
             if (t && (r = hipSetDevice(dev)) != hipSuccess) return;
+            if (t && own_streams && (r = hipStreamWaitEvent(stream, queued, 0)) != hipSuccess) return;
             int64_t from[2] = {0, 0}, count[2] = {0, 0};
             int turn = 0;
             auto finish = [&](int k) {
@@ -146,6 +152,8 @@ public:
             }
             finish(turn);
             finish(turn ^ 1);
+            // an error leaves kernels that may still use the buffer
+            if (r != hipSuccess) (void)hipStreamSynchronize(stream);
         };
         std::vector<std::thread> pool;
         int started = 1;
@@ -158,7 +166,6 @@ public:
         for (auto &th : pool) th.join();
         // chunks of threads that could not be started
         for (int t = started; t < threads; ++t) work(t, threads);
-        // an error leaves kernels that may still use the buffer
         const hipError_t done = hipStreamSynchronize(stream);
         for (hipError_t r : result)
             if (r != hipSuccess) return r;
