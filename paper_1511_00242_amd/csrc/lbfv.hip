@@ -94,7 +94,8 @@ struct PatchPlan {
 // caller's arrays and its slot of the buffer while other chunks are with the GPU.  Large fields
 // take several threads, each with two slots and its own chunks: one thread copies 5 to 10 GB/s
 // (the arrays' pages are often touched for the first time), the GPU's link 50.  The buffer and
-// its events belong to one context or batch and are kept until it is destroyed.
+// its events belong to one context or batch and are kept until it is destroyed; calls from several
+// threads (fields of one batch, say) take turns with them.
 class Transfer {
 public:
     // f(range, slot): enqueue the conversion kernel of `range` on the stream
@@ -104,6 +105,7 @@ public:
         // chunks of about 1 MiB; a thread per 2 MiB, at most 8 and half the CPUs
         int threads = (int)std::min<int64_t>({total >> 21, 8, (int64_t)std::thread::hardware_concurrency() / 2});
         threads = std::max(threads, 1);
+        const std::lock_guard<std::mutex> turn_of(mutex_);
         const int64_t chunk = threads == 1 && total <= kBuffer / 2 ? cells : std::max<int64_t>(1, (1 << 20) / width);
         if (chunk == cells) {
             // one chunk: the stream itself is waited for
@@ -181,6 +183,7 @@ public:
 
 private:
     static constexpr int64_t kBuffer = 16 << 20;   // most bytes kept
+    std::mutex mutex_;
     char *pinned_ = nullptr;
     size_t size_ = 0;
     std::vector<hipEvent_t> events_;
