@@ -96,14 +96,23 @@ struct PatchPlan {
 // (the arrays' pages are often touched for the first time), the GPU's link 50.  The buffer and
 // its events belong to one context or batch and are kept until it is destroyed; calls from several
 // threads (fields of one batch, say) take turns with them.
+// No allocation here can throw: the entry points pass no exception on.
+struct FieldArrays {   // arrays of one value per cell each
+    double *a[12];
+    int count = 0;
+    // `n` component arrays of one [n][ny][nx] array
+    void add(const double *f, int n, int64_t cells) {
+        for (int k = 0; k < n; ++k) a[count++] = const_cast<double *>(f) + k * cells;
+    }
+};
 class Transfer {
 public:
     // f(range, slot): enqueue the conversion kernel of `range` on the stream
     template <typename F>
-    hipError_t run(bool up, int64_t cells, const std::vector<double *> &arrays, hipStream_t stream, F f) {
-        const int64_t width = 8 * (int64_t)arrays.size(), total = cells * width;
+    hipError_t run(bool up, int64_t cells, const FieldArrays &arrays, hipStream_t stream, F f) {
+        const int64_t width = 8 * (int64_t)arrays.count, total = cells * width;
         // chunks of about 1 MiB; a thread per 2 MiB, at most 8 and half the CPUs
-        int threads = (int)std::min<int64_t>({total >> 21, 8, (int64_t)std::thread::hardware_concurrency() / 2});
+        int threads = (int)std::min<int64_t>({total >> 21, kThreads, (int64_t)std::thread::hardware_concurrency() / 2});
         threads = std::max(threads, 1);
         const std::lock_guard<std::mutex> turn_of(mutex_);
         const int64_t chunk = threads == 1 && total <= kBuffer / 2 ? cells : std::max<int64_t>(1, (1 << 20) / width);
@@ -128,7 +137,7 @@ public:
         const bool own_streams = stream == hipStreamPerThread && threads > 1;
         const hipEvent_t queued = events_[2 * threads];
         if (own_streams && (e = hipEventRecord(queued, stream)) != hipSuccess) return e;
-        std::vector<hipError_t> result(threads, hipSuccess);
+        hipError_t result[kThreads] = {};   // (hipSuccess)
         // thread t: chunks t, t + threads, ..., alternating between its two slots
         auto work = [&](int t, int stride) {
             hipError_t &r = result[t];
@@ -157,15 +166,14 @@ public:
             // an error leaves kernels that may still use the buffer
             if (r != hipSuccess) (void)hipStreamSynchronize(stream);
         };
-        std::vector<std::thread> pool;
+        std::thread pool[kThreads];
         int started = 1;
         try {
-            pool.reserve(threads);
-            for (; started < threads; ++started) pool.emplace_back(work, started, threads);
+            for (; started < threads; ++started) pool[started] = std::thread(work, started, threads);
         } catch (...) {
         }
         work(0, threads);
-        for (auto &th : pool) th.join();
+        for (int t = 1; t < started; ++t) pool[t].join();
         // chunks of threads that could not be started
         for (int t = started; t < threads; ++t) work(t, threads);
         const hipError_t done = hipStreamSynchronize(stream);
@@ -175,18 +183,19 @@ public:
     }
     void release() {
         if (pinned_) (void)hipHostFree(pinned_);
-        for (auto e : events_) (void)hipEventDestroy(e);
+        for (; nevents_ > 0; --nevents_) (void)hipEventDestroy(events_[nevents_ - 1]);
         pinned_ = nullptr;
         size_ = 0;
-        events_.clear();
     }
 
 private:
     static constexpr int64_t kBuffer = 16 << 20;   // most bytes kept
+    static constexpr int kThreads = 8;
     std::mutex mutex_;
     char *pinned_ = nullptr;
     size_t size_ = 0;
-    std::vector<hipEvent_t> events_;
+    hipEvent_t events_[2 * kThreads + 1];
+    int nevents_ = 0;
 
     double *slot(int k, int64_t bytes) const {
         return (double *)(pinned_ + std::min<int64_t>(k * bytes, (int64_t)size_ - bytes));
@@ -204,17 +213,14 @@ private:
             }
             size_ = bytes;
         }
-        while ((int)events_.size() < events) {
-            hipEvent_t ev;
-            if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return e;
-            events_.push_back(ev);
-        }
+        for (; nevents_ < events; ++nevents_)
+            if ((e = hipEventCreateWithFlags(&events_[nevents_], hipEventDisableTiming)) != hipSuccess) return e;
         return hipSuccess;
     }
-    static void copy(bool up, const std::vector<double *> &arrays, int64_t k0, int64_t n, double *buf) {
-        for (size_t a = 0; a < arrays.size(); ++a) {
-            if (up) memcpy(buf + a * n, arrays[a] + k0, n * 8);
-            else memcpy(arrays[a] + k0, buf + a * n, n * 8);
+    static void copy(bool up, const FieldArrays &arrays, int64_t k0, int64_t n, double *buf) {
+        for (int a = 0; a < arrays.count; ++a) {
+            if (up) memcpy(buf + a * n, arrays.a[a] + k0, n * 8);
+            else memcpy(arrays.a[a] + k0, buf + a * n, n * 8);
         }
     }
 };
@@ -1541,7 +1547,7 @@ void launch_field(const HostCase &h, const StepParams<T> &P, int parity, Field w
 // Move fields between the caller's arrays (one value per cell each) and the state in
 // buf[parity]; the stream is synchronised.
 hipError_t move_fields(const HostCase &h, int parity, Transfer &t, hipStream_t stream, Field which,
-                       const std::vector<double *> &arrays) {
+                       const FieldArrays &arrays) {
     double ext[4];
     current_ext(h, ext);
     StepParams<double> pd;
@@ -1557,9 +1563,19 @@ hipError_t move_fields(const HostCase &h, int parity, Transfer &t, hipStream_t s
         }
     });
 }
-// `count` component arrays of one [count][ny][nx] array
-void add_components(std::vector<double *> &arrays, const double *a, int count, const HostCase &h) {
-    for (int k = 0; k < count; ++k) arrays.push_back(const_cast<double *>(a) + (int64_t)k * h.nx * h.ny);
+// single arrays `one`, then arrays `three` of three components each
+FieldArrays field_arrays(const HostCase &h, std::initializer_list<const double *> one,
+                         std::initializer_list<const double *> three = {}) {
+    const int64_t n = (int64_t)h.nx * h.ny;
+    FieldArrays a;
+    for (const double *f : one) a.add(f, 1, n);
+    for (const double *f : three) a.add(f, 3, n);
+    return a;
+}
+FieldArrays state_arrays(const HostCase &h, const double *f) {
+    FieldArrays a;
+    a.add(f, 9, (int64_t)h.nx * h.ny);
+    return a;
 }
 template <typename Owner>
 int moved(Owner *o, hipError_t e, const char *what) {
@@ -1579,7 +1595,7 @@ void reref_t(lbfv_ctx *c, const RefState &from, const RefState &to) {
 }
 
 // a new state given by the caller's arrays
-int new_state(lbfv_ctx *c, Field which, const std::vector<double *> &arrays, const char *what) {
+int new_state(lbfv_ctx *c, Field which, const FieldArrays &arrays, const char *what) {
     int st = ensure_buffers(c);
     if (!st) st = moved(c, move_fields(c->hc, c->hc.cur, c->transfer, c->stream, which, arrays), what);
     if (st) return st;
@@ -1774,9 +1790,7 @@ int lbfv_bind_buffers(lbfv_ctx *c, void *a, void *b, size_t bytes) {
 int lbfv_init_equilibrium(lbfv_ctx *c, const double *rho, const double *ux, const double *uy) {
     if (!c) return LBFV_EINVAL;
     if (!rho || !ux || !uy) return c->fail(LBFV_EINVAL, "lbfv_init_equilibrium: NULL field");
-    std::vector<double *> a;
-    for (const double *f : {rho, ux, uy}) add_components(a, f, 1, c->hc);
-    return new_state(c, F_INIT_EQ, a, "init_equilibrium");
+    return new_state(c, F_INIT_EQ, field_arrays(c->hc, {rho, ux, uy}), "init_equilibrium");
 }
 
 int lbfv_init_chapman_enskog(lbfv_ctx *c, const double *rho, const double *ux, const double *uy,
@@ -1784,27 +1798,20 @@ int lbfv_init_chapman_enskog(lbfv_ctx *c, const double *rho, const double *ux, c
     if (!c) return LBFV_EINVAL;
     if (!rho || !ux || !uy || !drho || !dux || !duy)
         return c->fail(LBFV_EINVAL, "lbfv_init_chapman_enskog: NULL field");
-    std::vector<double *> a;
-    for (const double *f : {rho, ux, uy}) add_components(a, f, 1, c->hc);
-    for (const double *f : {drho, dux, duy}) add_components(a, f, 3, c->hc);
-    return new_state(c, F_INIT_CE, a, "init_chapman_enskog");
+    return new_state(c, F_INIT_CE, field_arrays(c->hc, {rho, ux, uy}, {drho, dux, duy}), "init_chapman_enskog");
 }
 
 int lbfv_set_f(lbfv_ctx *c, const double *f) {
     if (!c) return LBFV_EINVAL;
     if (!f) return c->fail(LBFV_EINVAL, "lbfv_set_f: NULL array");
-    std::vector<double *> a;
-    add_components(a, f, 9, c->hc);
-    return new_state(c, F_SET_F, a, "set_f");
+    return new_state(c, F_SET_F, state_arrays(c->hc, f), "set_f");
 }
 
 int lbfv_get_f(lbfv_ctx *c, double *f) {
     if (!c) return LBFV_EINVAL;
     if (!f) return c->fail(LBFV_EINVAL, "lbfv_get_f: NULL array");
     if (!c->has_state) return c->fail(LBFV_ESTATE, "no state");
-    std::vector<double *> a;
-    add_components(a, f, 9, c->hc);
-    return moved(c, move_fields(c->hc, c->hc.cur, c->transfer, c->stream, F_GET_F, a), "get_f");
+    return moved(c, move_fields(c->hc, c->hc.cur, c->transfer, c->stream, F_GET_F, state_arrays(c->hc, f)), "get_f");
 }
 
 int dugks_step(lbfv_ctx *c, int32_t n) { return do_steps(c, SCHEME_DUGKS, n); }
@@ -1819,7 +1826,8 @@ int lbfv_moments(lbfv_ctx *c, double *rho, double *ux, double *uy) {
     if (!c) return LBFV_EINVAL;
     if (!rho || !ux || !uy) return c->fail(LBFV_EINVAL, "lbfv_moments: NULL output");
     if (!c->has_state) return c->fail(LBFV_ESTATE, "no state");
-    return moved(c, move_fields(c->hc, c->hc.cur, c->transfer, c->stream, F_MOMENTS, {rho, ux, uy}), "moments");
+    const FieldArrays a = field_arrays(c->hc, {rho, ux, uy});
+    return moved(c, move_fields(c->hc, c->hc.cur, c->transfer, c->stream, F_MOMENTS, a), "moments");
 }
 
 int lbfv_totals(lbfv_ctx *c, double out[3]) {
@@ -2844,8 +2852,7 @@ int lbfv_batch_init_equilibrium(lbfv_batch *b, int32_t ci, const double *rho, co
     if (!b) return LBFV_EINVAL;
     if (ci < 0 || ci >= (int)b->cases.size() || !rho || !ux || !uy) return b->fail(LBFV_EINVAL, "bad case or field");
     const HostCase &h = b->cases[ci];
-    std::vector<double *> a;
-    for (const double *f : {rho, ux, uy}) add_components(a, f, 1, h);
+    const FieldArrays a = field_arrays(h, {rho, ux, uy});
     return moved(b, move_fields(h, b->parity, b->transfer, b->stream, F_INIT_EQ, a), "batch init_equilibrium");
 }
 
@@ -2853,24 +2860,21 @@ int lbfv_batch_set_f(lbfv_batch *b, int32_t ci, const double *f) {
     if (!b) return LBFV_EINVAL;
     if (ci < 0 || ci >= (int)b->cases.size() || !f) return b->fail(LBFV_EINVAL, "bad case or array");
     const HostCase &h = b->cases[ci];
-    std::vector<double *> a;
-    add_components(a, f, 9, h);
-    return moved(b, move_fields(h, b->parity, b->transfer, b->stream, F_SET_F, a), "batch set_f");
+    return moved(b, move_fields(h, b->parity, b->transfer, b->stream, F_SET_F, state_arrays(h, f)), "batch set_f");
 }
 
 int lbfv_batch_get_f(lbfv_batch *b, int32_t ci, double *f) {
     if (!b) return LBFV_EINVAL;
     if (ci < 0 || ci >= (int)b->cases.size() || !f) return b->fail(LBFV_EINVAL, "bad case or array");
     const HostCase &h = b->cases[ci];
-    std::vector<double *> a;
-    add_components(a, f, 9, h);
-    return moved(b, move_fields(h, b->parity, b->transfer, b->stream, F_GET_F, a), "batch get_f");
+    return moved(b, move_fields(h, b->parity, b->transfer, b->stream, F_GET_F, state_arrays(h, f)), "batch get_f");
 }
 
 int lbfv_batch_moments(lbfv_batch *b, int32_t ci, double *rho, double *ux, double *uy) {
     if (!b) return LBFV_EINVAL;
     if (ci < 0 || ci >= (int)b->cases.size() || !rho || !ux || !uy) return b->fail(LBFV_EINVAL, "bad case or output");
-    return moved(b, move_fields(b->cases[ci], b->parity, b->transfer, b->stream, F_MOMENTS, {rho, ux, uy}), "batch moments");
+    const FieldArrays a = field_arrays(b->cases[ci], {rho, ux, uy});
+    return moved(b, move_fields(b->cases[ci], b->parity, b->transfer, b->stream, F_MOMENTS, a), "batch moments");
 }
 
 int lbfv_batch_nonfinite(lbfv_batch *b, int32_t *count) {
