@@ -16,6 +16,7 @@
 #include <fstream>
 #include <map>
 #include <mutex>
+#include <new>
 #include <sstream>
 #include <string>
 #include <thread>
@@ -2320,16 +2321,24 @@ bool plan_batch_patches(const lbfv_batch *b, int max_waves, int halo, std::vecto
     }
     return count < (1 << 24);
 }
-void drop_patches(lbfv_batch::Patches &p) {
+// (with the graphs whose launches name their tables)
+void drop_patches(lbfv_batch *b, int scheme) {
+    for (auto &g : b->gexec[2 + scheme])
+        if (g) {
+            (void)hipGraphExecDestroy(g);
+            g = nullptr;
+        }
+    lbfv_batch::Patches &p = b->patches[scheme];
     if (p.d_grids) (void)hipFree(p.d_grids);
     if (p.d_items) (void)hipFree(p.d_items);
     p = lbfv_batch::Patches();
 }
 // Put the patches of a halo width (0: the cost model's choice of it) and workgroup size in place;
-// without any that every case takes, waves stays 0.
-int make_patches(lbfv_batch *b, int scheme, int halo, int max_waves) {
+// without any that every case takes, waves stays 0.  So it does where there is no memory for
+// their tables: the batch marches then, which needs none.
+int make_patches_or_throw(lbfv_batch *b, int scheme, int halo, int max_waves) {
     lbfv_batch::Patches &out = b->patches[scheme];
-    drop_patches(out);
+    drop_patches(b, scheme);
     out.halo = std::max(halo, 1);
     const bool f64 = is_f64(b->variant);
     const PatchDevice dev = patch_device(f64, batch_patch_fn_variant(b->variant, scheme, b->bnd));
@@ -2357,15 +2366,25 @@ int make_patches(lbfv_batch *b, int scheme, int halo, int max_waves) {
     if (hipMalloc((void **)&out.d_grids, best.size() * sizeof(PatchGrid)) != hipSuccess ||
         hipMalloc((void **)&out.d_items, items.size() * sizeof(PatchItem)) != hipSuccess) {
         (void)hipGetLastError();
-        drop_patches(out);
-        return b->fail(LBFV_ENOMEM, "batch: cannot allocate the patch list");
+        drop_patches(b, scheme);
+        out.halo = std::max(halo, 1);
+        return LBFV_OK;
     }
     if (hipMemcpy(out.d_grids, best.data(), best.size() * sizeof(PatchGrid), hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(out.d_items, items.data(), items.size() * sizeof(PatchItem), hipMemcpyHostToDevice) != hipSuccess) {
-        drop_patches(out);
+        drop_patches(b, scheme);
         return b->fail(LBFV_EHIP, "batch: patch list upload failed");
     }
     return LBFV_OK;
+}
+int make_patches(lbfv_batch *b, int scheme, int halo, int max_waves) {
+    try {
+        return make_patches_or_throw(b, scheme, halo, max_waves);
+    } catch (const std::bad_alloc &) {
+        drop_patches(b, scheme);
+        b->patches[scheme].halo = std::max(halo, 1);
+        return LBFV_OK;
+    }
 }
 
 // Whether the patch form advances the batch: asked for by the autotuner, or by the sizes of the
@@ -2620,7 +2639,7 @@ int lbfv_batch_destroy(lbfv_batch *b) {
     for (auto &h : b->cases) free_case(h);
     if (b->d_params) (void)hipFree(b->d_params);
     if (b->d_items) (void)hipFree(b->d_items);
-    for (auto &p : b->patches) drop_patches(p);
+    for (int scheme : {0, 1}) drop_patches(b, scheme);
     b->transfer.release();
     delete b;
     return LBFV_OK;
@@ -2824,7 +2843,7 @@ int lbfv_batch_autotune(lbfv_batch *b, int scheme, int32_t trial_steps, double *
     (void)hipFree(save);
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
-    drop_patches(b->patches[scheme]);
+    drop_patches(b, scheme);
     b->form = st ? form0 : FORM_MARCH;
     if (st) return st;
     if (st2) return st2;
@@ -2832,7 +2851,7 @@ int lbfv_batch_autotune(lbfv_batch *b, int scheme, int32_t trial_steps, double *
     if ((st = batch_set_time_block(b, best_tb))) return st;
     if (patch_halo) {
         if ((st = make_patches(b, scheme, patch_halo, patch_waves))) return st;
-        b->form = FORM_PATCH;
+        if (b->patches[scheme].waves) b->form = FORM_PATCH;
     }
     batch_drop_graphs(b);
     if (best_ms) *best_ms = best;
