@@ -2370,21 +2370,28 @@ int make_patches_or_throw(lbfv_batch *b, int scheme, int halo, int max_waves) {
         out.halo = std::max(halo, 1);
         return LBFV_OK;
     }
-    if (hipMemcpy(out.d_grids, best.data(), best.size() * sizeof(PatchGrid), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(out.d_items, items.data(), items.size() * sizeof(PatchItem), hipMemcpyHostToDevice) != hipSuccess) {
+    if (hipMemcpyAsync(out.d_grids, best.data(), best.size() * sizeof(PatchGrid), hipMemcpyHostToDevice, b->stream) != hipSuccess ||
+        hipMemcpyAsync(out.d_items, items.data(), items.size() * sizeof(PatchItem), hipMemcpyHostToDevice, b->stream) != hipSuccess ||
+        hipStreamSynchronize(b->stream) != hipSuccess) {
         drop_patches(b, scheme);
         return b->fail(LBFV_EHIP, "batch: patch list upload failed");
     }
     return LBFV_OK;
 }
+// The first steps of a batch come here: the thread may be capturing work on another stream, which
+// an allocation would break off but for the relaxed mode.
 int make_patches(lbfv_batch *b, int scheme, int halo, int max_waves) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    int st = LBFV_OK;
     try {
-        return make_patches_or_throw(b, scheme, halo, max_waves);
+        st = make_patches_or_throw(b, scheme, halo, max_waves);
     } catch (const std::bad_alloc &) {
         drop_patches(b, scheme);
         b->patches[scheme].halo = std::max(halo, 1);
-        return LBFV_OK;
     }
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return st;
 }
 
 // Whether the patch form advances the batch: asked for by the autotuner, or by the sizes of the
