@@ -707,6 +707,17 @@ constexpr int64_t BATCH_PATCH_CELLS = 1 << 18;
 // launch) pass the patch form between 200^2 and 450^2 cells.
 constexpr int64_t PATCH_TRIAL_CELLS = 1 << 20;
 
+// Largest mesh on which a launch of one step takes patches; above, a march of one step (in the same
+// layout, with the same bits) comes cheaper than a halo made for several.  us a call of one step,
+// patches and marches: FP64 DUGKS periodic 640^2 21.7 and 25.6, 680^2 29.6 and 25.3, BKG 570^2 19.3
+// and 22.8, 600^2 25.3 and 22.9; FP32 DUGKS 720^2 17.9 and 21.3, 1000^2 37.9 and 30.7, cavity 800^2
+// 28.7 and 29.1, 1000^2 48.0 and 37.2; BKG 640^2 14.9 and 16.1, 680^2 19.5 and 16.3, cavity 680^2
+// 20.0 and 24.8, 800^2 29.7 and 25.1.
+int64_t patch_single_cells(bool f64, int scheme) { return f64 ? 340000 : (scheme == SCHEME_BKG ? 440000 : 640000); }
+// And the cells of all cases of a batch.  FP64 224 x 32^2 18.3 (cavities, DUGKS) and 23.5, 512^2 24.9
+// and 19.4; FP32 512^2 14.2 and 16.8, 8 x 256^2 26.7 and 21.4, 24 of 64^2 to 512^2 105 and 56.
+int64_t batch_single_cells(bool f64) { return f64 ? 240000 : 350000; }
+
 // Patches of at most 64 / per_wave columns and waves x per_wave rows with the given halo.
 bool plan_patch(const HostCase &h, int per_wave, int waves, int halo, PatchPlan &p) {
     PatchGrid &g = p.g;
@@ -1386,6 +1397,7 @@ int set_layout(lbfv_ctx *c, int w) {
 // that names that buffer).
 struct Advance {
     bool patch = false, exact = false;
+    bool single_marches = false;   // patches, but marches for the launches of one step
     int per = 1;
 };
 // The steps per launch of marches where no shape was set: a chain of four waves on a doubly
@@ -1435,6 +1447,7 @@ int plan_advance(lbfv_ctx *c, int scheme, int n, Advance &a) {
         const PatchPlan &p = patch_plan(c, scheme);
         a.patch = p.waves > 0;
         if (a.patch) a.per = p.g.halo;
+        a.single_marches = a.patch && cells > patch_single_cells(is_f64(h.variant), scheme);
     }
     return LBFV_OK;
 }
@@ -1486,7 +1499,8 @@ int do_steps(lbfv_ctx *c, int scheme, int32_t n) {
     const bool patch = adv.patch;
     const int per = adv.per;
     auto launch = [&](int steps) {
-        int ls = patch ? launch_patch(c, scheme, h.cur, ext, steps) : launch_one(c, scheme, h.cur, ext, steps);
+        const bool as_patch = patch && !(steps == 1 && adv.single_marches);
+        int ls = as_patch ? launch_patch(c, scheme, h.cur, ext, steps) : launch_one(c, scheme, h.cur, ext, steps);
         if (!ls) h.cur ^= 1;
         return ls;
     };
@@ -1510,14 +1524,11 @@ int do_steps(lbfv_ctx *c, int scheme, int32_t n) {
             h.cur ^= (c->gsteps & 1);
             left -= per * c->gsteps;
         }
-        // The steps left over: launches of `per` steps and one of fewer, in the same strip layout
-        // (every narrower march fits a wider halo's strip); or an even or odd number of launches
-        // as the steps are, none of them shorter than need be.
-        for (int launches = tail_launches(left, per, adv.exact); launches > 0; --launches) {
-            const int k = launch_steps(left, launches, per, adv.exact);
+        // the steps left over, in the same strip layout (every narrower march fits a wider halo's
+        // strip)
+        Cut cut(left, per, adv.exact, patch && adv.single_marches);
+        while (const int k = cut.next())
             if ((st = launch(k))) return st;
-            left -= k;
-        }
         c->steps += seg;
         n -= seg;
         if (c->check_every > 0 && c->steps - c->steps_at_check >= c->check_every) {
@@ -2964,12 +2975,15 @@ int lbfv_batch_step(lbfv_batch *b, int scheme, int32_t n) {
         n -= (int32_t)(per * replay);
     }
     // (patches: an even or odd number of launches as the steps are, like one-step launches)
-    for (int launches = tail_launches(n, per, patch); launches > 0; --launches) {
-        const int k = launch_steps(n, launches, per, patch);
-        st = patch ? batch_launch_patches(b, scheme, b->parity, k) : batch_launch_one(b, scheme, b->parity, k == 2);
+    int64_t cells = 0;
+    for (const auto &h : b->cases) cells += (int64_t)h.nx * h.ny;
+    const bool single_marches = patch && cells > batch_single_cells(is_f64(b->variant));
+    Cut cut(n, per, patch, single_marches);
+    while (const int k = cut.next()) {
+        st = patch && !(k == 1 && single_marches) ? batch_launch_patches(b, scheme, b->parity, k)
+                                                  : batch_launch_one(b, scheme, b->parity, k == 2);
         if (st) return st;
         b->parity ^= 1;
-        n -= k;
     }
     return LBFV_OK;
 }

@@ -1,0 +1,92 @@
+"""Calls of a few steps on meshes that take patches in longer ones: one step is marched where that
+is faster, and calls that mix patches and marches keep the bits and the buffer."""
+import os
+import sys
+
+import numpy as np
+import pytest
+
+from paper_1511_00242_amd import inputs as I
+from paper_1511_00242_amd import lbfv as L
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+from test_gpu_layouts import kernels_of  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+FORMS = {"f64": (L.LBFV_FP64, L.LBFV_STORE_NATIVE), "f32": (L.LBFV_FP32, L.LBFV_STORE_DEV_FP32),
+         "f16": (L.LBFV_FP32, L.LBFV_STORE_DEV_FP16)}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need an MI355X"
+    torch.cuda.set_device(0)
+    yield
+
+
+def steps_run(call):
+    return {n for n in kernels_of(call) if "patch" in n or "step" in n or "lbfv::batch" in n}
+
+
+@pytest.mark.parametrize("form,scheme,n", [("f64", L.LBFV_BKG, 620), ("f32", L.LBFV_BKG, 700),
+                                           ("f32", L.LBFV_DUGKS, 900), ("f16", L.LBFV_BKG, 1000)])
+def test_single_steps_of_larger_meshes_are_marched(form, scheme, n):
+    w = I.taylor_green(n)
+    compute, storage = FORMS[form]
+    with L.Context(w.xf, w.yf, w.tau, w.dt, bcs=w.bcs, compute=compute, storage=storage, check_every=0) as ctx:
+        ctx.init_equilibrium(w.rho, w.ux, w.uy)
+        one, five = (steps_run(lambda: ctx.step(scheme, k)) for k in (1, 9))
+        assert one and not any("patch" in k for k in one), one
+        assert any("patch" in k for k in five), five
+
+
+def test_single_steps_of_larger_batches_are_marched():
+    cases = [I.taylor_green(512)] * 2
+    b = L.Batch(cases)
+    for i, w in enumerate(cases):
+        b.init_equilibrium(i, w.rho, w.ux, w.uy)
+    one, nine = (steps_run(lambda: b.step(L.LBFV_DUGKS, k)) for k in (1, 9))
+    b.close()
+    assert one and not any("patch" in k for k in one), one
+    assert any("patch" in k for k in nine), nine
+
+
+# just above the sizes from which single steps are marched
+@pytest.mark.parametrize("form,kind,n", [("f64", "vortex", 600), ("f32", "vortex", 820), ("f32", "cavity", 820),
+                                         ("f16", "vortex", 820)])
+def test_short_calls_keep_the_bits(form, kind, n):
+    w = I.cavity(n, stretched=False) if kind == "cavity" else I.taylor_green(n)
+    compute, storage = FORMS[form]
+    outs = []
+    for march in (True, False):
+        with L.Context(w.xf, w.yf, w.tau, w.dt, bcs=w.bcs, compute=compute, storage=storage, check_every=4) as ctx:
+            ctx.init_equilibrium(w.rho, w.ux * 10 + 0.01, w.uy * 10)
+            if march:
+                ctx.set_tile(16, 4)
+            for k in (1, 2, 3, 4, 5, 8, 11):
+                ctx.step(L.LBFV_DUGKS if k & 1 else L.LBFV_BKG, k)
+            outs.append(ctx.get_f())
+    assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("form", ["f64", "f32"])
+def test_short_calls_of_batches_keep_the_bits(form):
+    compute, storage = FORMS[form]
+    cases = [I.taylor_green(512), I.cavity(300, stretched=False), I.taylor_green(64)]
+    for scheme in (L.LBFV_DUGKS, L.LBFV_BKG):
+        outs = []
+        for march in (True, False):
+            b = L.Batch(cases, compute=compute, storage=storage)
+            for i, w in enumerate(cases):
+                b.init_equilibrium(i, w.rho, w.ux * 10 + 0.01, w.uy * 10)
+            b.set_shape(graph_steps=3)
+            if march:
+                b.set_shape(rows=5)
+            for k in (1, 2, 3, 4, 5, 8, 11, 29):
+                b.step(scheme, k)
+            outs.append([b.get_f(i) for i in range(len(cases))])
+            b.close()
+        for f, g in zip(*outs):
+            assert np.array_equal(f, g)

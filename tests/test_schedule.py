@@ -15,8 +15,12 @@ def sched(tmp_path_factory):
     src, so = d / "s.cpp", d / "s.so"
     src.write_text("""#include "schedule.hpp"
 extern "C" {
-int tail(int n, int per, int exact) { return lbfv::tail_launches(n, per, exact); }
-int steps(int left, int launches, int per, int exact) { return lbfv::launch_steps(left, launches, per, exact); }
+int cut(int n, int per, int exact, int no_twos, int *out) {
+    lbfv::Cut c(n, per, exact, no_twos);
+    int count = 0;
+    while (const int k = c.next()) out[count++] = k;
+    return count;
+}
 int trial(int per, int n) { return lbfv::trial_length(per, n); }
 }
 """)
@@ -24,13 +28,10 @@ int trial(int per, int n) { return lbfv::trial_length(per, n); }
     return C.CDLL(str(so))
 
 
-def cut(sched, n, per, exact):
-    out, launches = [], sched.tail(n, per, exact)
-    for left in range(launches, 0, -1):
-        k = sched.steps(n, left, per, exact)
-        out.append(k)
-        n -= k
-    assert n == 0
+def cut(sched, n, per, exact, no_twos=0):
+    out = (C.c_int * (n + 8))()
+    out = list(out[:sched.cut(n, per, exact, no_twos, out)])
+    assert sum(out) == n
     return out
 
 
@@ -40,6 +41,9 @@ def test_calls_are_cut_into_launches(sched, per):
         even = cut(sched, n, per, 1)
         assert all(1 <= k <= per for k in even) and (len(even) - n) % 2 == 0
         assert len(even) <= -(-n // per) + 1 and (not even or max(even) - min(even) <= 1)
+        mixed = cut(sched, n, per, 1, 1)
+        assert all(1 <= k <= per for k in mixed) and (len(mixed) - n) % 2 == 0 and len(mixed) <= len(even)
+        assert mixed == even if per < 3 else 2 not in mixed
         plain = cut(sched, n, per, 0)
         assert len(plain) == -(-n // per) and all(k == per for k in plain[:-1])
 
