@@ -905,8 +905,10 @@ int default_rows(const HostCase &h, int scheme, int wpb, int tb = 1, bool pairs 
         if (best) return best;
     }
     if (cells >= (1 << 22)) {
-        // large meshes: one round of resident waves
-        auto r = balanced_rows(h, resident_waves(step_fn_variant(h.variant, scheme, bnd, ref), wpb), STRIP1);
+        // large meshes: one round of resident waves, of the strips that the state is laid out in now
+        // (heights made for 62 columns overflow the round in 56: 4096^2 FP64 DUGKS, one step a call
+        // after a long one, 652 us, and 565 with heights made for 56)
+        auto r = balanced_rows(h, resident_waves(step_fn_variant(h.variant, scheme, bnd, ref), wpb), h.strip);
         if (!r.empty()) return r[0];
         return std::min(64, h.ny);
     }
@@ -1388,6 +1390,7 @@ int set_layout(lbfv_ctx *c, int w) {
     }
     h.set_strip(w);
     drop_graphs(c);
+    memset(c->rows_of, 0, sizeof(c->rows_of));
     return LBFV_OK;
 }
 

@@ -90,3 +90,18 @@ def test_short_calls_of_batches_keep_the_bits(form):
             b.close()
         for f, g in zip(*outs):
             assert np.array_equal(f, g)
+
+
+def test_heights_of_one_step_follow_the_layout():
+    """After a long call the strips are narrower and more: the row blocks of one-step launches
+    still fill one round of resident waves, and no part of a second one."""
+    w = I.taylor_green(2100)
+    items = []
+    with L.Context(w.xf, w.yf, w.tau, w.dt, bcs=w.bcs, check_every=0) as ctx:
+        ctx.init_equilibrium(w.rho, w.ux, w.uy)
+        for strip in (62, 56):
+            rows = ctx.get_tile()[0]
+            items.append(-(-w.nx // strip) * -(-w.ny // rows))
+            ctx.dugks_step(32)
+    print(items)
+    assert items[1] <= items[0] * 1.03
