@@ -242,6 +242,7 @@ struct lbfv_ctx {
     int rows_of[2][5][2] = {};       // default_rows of the BKG / other kernels, time block and pairs (0: not asked yet)
     bool pinned = false;             // a program may hold captured work on the state's layout, or owns the
                                      // buffers: keep it
+    int64_t singles = 0;             // one-step launches in a row in the layout of several (no shape set)
     // graphs of `gsteps` launches, per scheme (+4 per further step per launch) and starting buffer
     int gsteps = 32;
     // (16 + scheme: the patch form)
@@ -1418,6 +1419,9 @@ int64_t patch_cells(const HostCase &h, int scheme) {
     return f64 ? 170000 : (has_boundary(h) ? 360000 : 350000);
 }
 constexpr int LONG_CALL = 16;   // steps from which moving the state to another layout pays
+// One-step launches in a row after which moving it back to 62 columns pays: a launch takes 5 to 10 %
+// longer in 56 or 60 on large meshes, and the move about as long as a launch.
+constexpr int SINGLES_BACK = 8;
 int plan_advance(lbfv_ctx *c, int scheme, int n, Advance &a) {
     HostCase &h = c->hc;
     const int64_t cells = (int64_t)h.nx * h.ny;
@@ -1438,9 +1442,18 @@ int plan_advance(lbfv_ctx *c, int scheme, int n, Advance &a) {
     const bool wide = h.variant == V_F64 || h.variant == V_F32;
     if (c->form == FORM_AUTO && wide && cells > patch_cells(h, scheme) && !one_step_only(h)) {
         const int tb = unasked_time_block(h), strip = SLOTS - 2 * tb;
-        if (h.strip == strip || (n >= LONG_CALL && !c->pinned)) {
+        // calls, or intervals between checks, so short that their parity leaves single steps only
+        // (2 of a chain's, 3 of a pair's)
+        const bool singles = (c->check_every > 0 ? std::min(n, c->check_every) : n) <= (tb == 2 ? 3 : 2);
+        if (!singles && (h.strip == strip || (n >= LONG_CALL && !c->pinned))) {
             a.per = tb;
+            c->singles = 0;
             return set_layout(c, strip);
+        }
+        if (!singles) c->singles = 0;
+        else if (h.strip != STRIP1 && !c->pinned && (c->singles += n) > SINGLES_BACK) {
+            int st = set_layout(c, STRIP1);
+            if (st) return st;
         }
     }
     // (short calls on larger meshes: patches too, but for FP64 with sides, whose few resident

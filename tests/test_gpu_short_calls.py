@@ -105,3 +105,32 @@ def test_heights_of_one_step_follow_the_layout():
             ctx.dugks_step(32)
     print(items)
     assert items[1] <= items[0] * 1.03
+
+
+@pytest.mark.parametrize("kind,few", [("vortex", 2), ("cavity", 3)])
+def test_single_steps_move_the_state_back(kind, few):
+    """Calls too short for launches of several steps, many in a row after a long one: the state
+    goes back to the strips of one-step launches, and to the others in the next long call.  A
+    program that holds captured work keeps the layout."""
+    import torch
+    w = I.cavity(1100, stretched=False) if kind == "cavity" else I.taylor_green(1100)
+    moved = lambda call: any("relayout" in k for k in kernels_of(call))   # noqa: E731
+    outs = []
+    for how in ("march", "auto", "captured"):
+        with L.Context(w.xf, w.yf, w.tau, w.dt, bcs=w.bcs, check_every=0) as ctx:
+            ctx.init_equilibrium(w.rho, w.ux, w.uy)
+            if how == "march":
+                ctx.set_tile(24, 4)
+                ctx.dugks_step(32 + 12 * few + 32 + 1 + 4)
+                outs.append(ctx.get_f())
+                continue
+            assert moved(lambda: ctx.dugks_step(32))
+            if how == "captured":
+                out = torch.zeros(4, dtype=torch.float64, device="cuda")
+                ctx.totals_device(out.data_ptr())
+            back = [moved(lambda: ctx.dugks_step(few)) for _ in range(12)]
+            assert back.count(True) == (how == "auto") and not any(back[:8 // few])
+            assert moved(lambda: ctx.dugks_step(32)) == (how == "auto")
+            assert not moved(lambda: ctx.dugks_step(1)) and not moved(lambda: ctx.dugks_step(4))
+            outs.append(ctx.get_f())
+    assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
