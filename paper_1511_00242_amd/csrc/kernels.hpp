@@ -500,15 +500,47 @@ struct March {
     // constants spilled from the scalar registers in every strip (73 of them in the FP64 DUGKS
     // pair, 3 now): 1024^2 cavity FP64 DUGKS, pairs, 27.9 -> 25.8 us a step, 96-case FP32 batch
     // 141 -> 119.
+    // SELECT: the same rule in one form for all kinds, a side's constants loaded once per row.  It
+    // needs fewer vector registers: BKG's two steps on one wave in FP32 arithmetic take 132 of them
+    // with branches and 121 so, and up to 128 a fourth wave fits a SIMD (2500^2 cavity, 16 rows, 24
+    // steps a call: 1620 and 1550 us; the other kernels keep their waves, or gain one, with branches).
+    static constexpr bool kSelectGhosts = sizeof(T) == 4 && SCHEME == SCHEME_BKG;
+    struct GhostRule {
+        bool mirror, inflow;
+        T e, c[9];
+    };
+    __device__ __forceinline__ GhostRule ghost_rule(int side) const {
+        GhostRule r;
+        const int k = P.bc[side];
+        r.mirror = k == BC_SYMMETRY;
+        r.inflow = k == BC_INFLOW;
+        r.e = P.gext[side];
+#pragma unroll
+        for (int a = 0; a < 9; ++a) r.c[a] = P.gin[side][a];
+        return r;
+    }
+    __device__ __forceinline__ static T ghost_value(const GhostRule &r, int A, T g1, T g2, T gm) {
+        T g = fma(g1 - g2, r.e, g1);
+        g = r.inflow ? r.c[A] : g;
+        return r.mirror ? gm : g;
+    }
     // x-side ghost lanes of one row (x-sides first, as in Sec. 2.5 reading R5)
     template <int STEP>
     __device__ __forceinline__ static T inward(T v) { return STEP > 0 ? shl1(v) : shr1(v); }
-    template <int STEP>
+    template <int STEP, bool SELECT>
     __device__ __forceinline__ void ghost_lane(int side, int at, T (&phi)[9]) const {
         // only the ghost lane is written, and it reads its interior neighbours, so the
         // directions may be filled in place in any order
         const int k = P.bc[side];
-        if (k == BC_INFLOW) {
+        if constexpr (SELECT) {
+            const GhostRule r = ghost_rule(side);
+#pragma unroll
+            for (int a = 0; a < 9; ++a) {
+                const T g1 = inward<STEP>(phi[a]), g2 = inward<STEP>(g1);
+                const T g = ghost_value(r, a, g1, g2, inward<STEP>(phi[MIRX[a]]));
+                phi[a] = lane == at ? g : phi[a];
+            }
+        } else if (k == BC_INFLOW) {
 #pragma unroll
             for (int a = 0; a < 9; ++a) phi[a] = lane == at ? P.gin[side][a] : phi[a];
         } else if (k == BC_SYMMETRY) {
@@ -527,15 +559,28 @@ struct March {
             }
         }
     }
+    template <bool SELECT = false>
     __device__ __forceinline__ void ghost_x(T (&phi)[9]) const {
         if constexpr (BND) {
-            if (ghostW) ghost_lane<1>(SIDE_W, HALO - 1, phi);
-            if (ghostE) ghost_lane<-1>(SIDE_E, laneE, phi);
+            if (ghostW) ghost_lane<1, SELECT>(SIDE_W, HALO - 1, phi);
+            if (ghostE) ghost_lane<-1, SELECT>(SIDE_E, laneE, phi);
         }
     }
     // y-side ghost row from rows r1 (adjacent) and r2 (next); ghost lanes included (corners).
     // Lanes in the side's wall segment take the wall rule.
+    template <bool SELECT = false>
     __device__ __forceinline__ void ghost_y(int side, const T (&r1)[9], const T (&r2)[9], T (&out)[9]) const {
+        if constexpr (SELECT) {
+            const bool seg = side == SIDE_S ? segS : segN;
+            const GhostRule r = ghost_rule(side);
+            const T ext = P.ext[side];
+#pragma unroll
+            for (int a = 0; a < 9; ++a) {
+                const T g = ghost_value(r, a, r1[a], r2[a], r1[MIRY[a]]);
+                out[a] = seg ? fma(r1[a] - r2[a], ext, r1[a]) : g;
+            }
+            return;
+        }
         const int k = P.bc[side];
         if (k == BC_INFLOW) {
 #pragma unroll
@@ -761,7 +806,7 @@ struct March {
         T v[9];
         advance(r, Pm, P0, Pp, S0, fS, v);     // level 1 of row k
         cell_t(v, Qk, Uk);
-        ghost_x(Qk);
+        ghost_x<kSelectGhosts>(Qk);
         if (PHASE < 0 ? k == j0 : PHASE == 1) {
             yface(j0, Qm1, Qk, gS);           // level-1 face south of row j0
             face_mix<1>(gS);
@@ -772,7 +817,7 @@ struct March {
         }
         if (need_next) {
             cell(R, Pm, Sm);
-            ghost_x(Pm);
+            ghost_x<kSelectGhosts>(Pm);
         }
     }
 
@@ -835,11 +880,11 @@ struct March {
         load(j0 - 1, R1);
         load(j0, R2);
         cell(R, PA, SA);
-        ghost_x(PA);
+        ghost_x<kSelectGhosts>(PA);
         cell(R1, PB, SB);
-        ghost_x(PB);
+        ghost_x<kSelectGhosts>(PB);
         cell(R2, PC, SC);
-        ghost_x(PC);
+        ghost_x<kSelectGhosts>(PC);
         yface(row_index(j0 - 1), PA, PB, fS);
         face_mix<1>(fS);
 
@@ -1061,15 +1106,15 @@ struct March {
         load(a, R1);
         load(a + 1, R2);
         cell(R1, P0, S0);
-        ghost_x(P0);
+        ghost_x<kSelectGhosts>(P0);
         cell(R2, Pp, Sp);
-        ghost_x(Pp);
+        ghost_x<kSelectGhosts>(Pp);
         if (ghostS0) {
-            ghost_y(SIDE_S, P0, Pp, Pm);
+            ghost_y<kSelectGhosts>(SIDE_S, P0, Pp, Pm);
         } else {
             T Sx[9];
             cell(R, Pm, Sx);
-            ghost_x(Pm);
+            ghost_x<kSelectGhosts>(Pm);
         }
         yface(row_index(a), Pm, P0, fS);
         if (ghostS0) south_sides(fS);
@@ -1089,10 +1134,10 @@ struct March {
             copy9(Qm1, Q0);
             copy9(Um1, U0);
             cell_t(v, Q0, U0);
-            ghost_x(Q0);
+            ghost_x<kSelectGhosts>(Q0);
             if (clipS && k == 1) {
                 // level-1 ghost row -1 from rows 0 and 1, then the south face of row 0
-                ghost_y(SIDE_S, Qm1, Q0, Qm2);
+                ghost_y<kSelectGhosts>(SIDE_S, Qm1, Q0, Qm2);
                 yface(0, Qm2, Qm1, gS);
                 south_sides(gS);
                 face_mix<1>(gS);
@@ -1111,17 +1156,17 @@ struct March {
                 copy9(P0, Pp);
                 copy9(S0, Sp);
                 if (!per_y && k + 2 == ny) {
-                    ghost_y(SIDE_N, P0, Pm, Pp);
+                    ghost_y<kSelectGhosts>(SIDE_N, P0, Pm, Pp);
                 } else {
                     cell(R, Pp, Sp);
-                    ghost_x(Pp);
+                    ghost_x<kSelectGhosts>(Pp);
                 }
             }
         }
         if (clipN) {
             // level-1 ghost row ny from rows ny-1 and ny-2, then the update of row ny-1
             T Qg[9], w[9];
-            ghost_y(SIDE_N, Q0, Qm1, Qg);
+            ghost_y<kSelectGhosts>(SIDE_N, Q0, Qm1, Qg);
             advance(ny - 1, Qm1, Q0, Qg, U0, gS, w);
             store_row(ny - 1, w);
         }
