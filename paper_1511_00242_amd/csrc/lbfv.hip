@@ -845,6 +845,16 @@ void fill_args(const HostCase &h, const double ext[4], const StepShape &sh, int 
     a.bind(is_f64(h.variant));
 }
 
+// compute units of the current device (0: unknown)
+int device_cus() {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
+        return n;
+    (void)hipGetLastError();
+    return 0;
+}
+
 // Wave slots the step kernel can keep resident on the whole device (CUs x waves per CU).
 int resident_waves(void *fn, int wpb) {
     int dev = 0, blocks = 0;
@@ -875,20 +885,49 @@ std::vector<int> balanced_rows(const HostCase &h, int slots, int strip, int kmax
     return out;
 }
 
+// Rows of the row blocks of chains of tb waves where none were set.  With `load` chains on a CU, as
+// many as all its items need, a launch takes (rows + 3 tb)(1 + x waves) units: an item's own rows and
+// those that fill and drain its levels, each longer by x for every wave on the fullest SIMD (300^2
+// and 450^2, 2 to 17 rows; more chains than are resident take turns).  One chain per CU on
+// small meshes is then better than all that fit: 300^2 FP64 DUGKS 8 rows (228 items) 5.25 us a step,
+// 6 (300) 6.27, 4 (450) 5.59.  In FP32 arithmetic blocks of more than 100 rows lose to more rounds:
+// 4096^2 FP32 DUGKS 316, 122 and 64 rows 173, 159 and 163 us, FP16 173, 157 and 161.
+int chain_rows(const HostCase &h, int scheme, int tb, int resident, int cus) {
+    const int strip = SLOTS - 2 * tb, nstrips = (h.nx + strip - 1) / strip;
+    const int fit = std::max(1, resident / cus);   // chains of a CU
+    const bool f64 = is_f64(h.variant), bkg = scheme == SCHEME_BKG;
+    const double x = f64 ? (bkg ? 0.32 : 0.49) : (bkg ? 0.17 : 0.21);
+    int best = 0;
+    double least = 0;
+    for (int load = 1; load <= 8 * fit; ++load) {
+        const int blocks = (int)std::min<int64_t>((int64_t)load * cus / nstrips, h.ny);
+        if (blocks < 1) continue;
+        const int rows = (h.ny + blocks - 1) / blocks, rest = load % fit;
+        if (!f64 && rows > 100 && load < 8 * fit) continue;
+        auto share = [&](int chains) { return (tb * chains + 3) / 4; };   // waves on the fullest SIMD
+        const double cost = (rows + 3 * tb) * (load / fit * (1 + x * share(fit)) + (rest ? 1 + x * share(rest) : 0));
+        if (!best || cost < least) {
+            best = rows;
+            least = cost;
+        }
+    }
+    return best;
+}
+
 // Row-block height of a march whose height was not set.  One step per launch: 8 or 16 rows, and
-// on large meshes one round of resident waves.  Several steps per launch: k whole rounds of
-// resident work items (waves, pairs or chains), k such that the rows a slot marches are fewest,
-// each item's own and the 3 tb that fill and drain its levels.  That is the autotuner's choice to
-// within a few rows (4096^2 FP64 DUGKS, chains of four: 205 rows; 1024^2: 40; 512^2: 11), where
-// the one-step heights of 8 and 16 rows ran a chain of four on 1536^2 FP16 at 35.2 us a step
-// against 28.5.
+// on large meshes one round of resident waves.  Two steps per launch: k whole rounds of resident
+// work items (waves or pairs), k such that the rows a slot marches are fewest, each item's own and
+// the 6 that fill and drain its levels (1024^2 FP64 DUGKS: 40 rows; 512^2: 11).
 int default_rows(const HostCase &h, int scheme, int wpb, int tb = 1, bool pairs = false) {
     const int64_t cells = (int64_t)h.nx * h.ny;
     const bool bnd = !(h.periodic_x() && h.periodic_y()), ref = ref_terms(h);
-    if (tb >= 2) {
-        const int slots = tb >= 3 ? resident_waves(stepc_fn_variant(h.variant, scheme, tb, ref), tb) / tb
-                          : pairs ? resident_waves(step2p_fn_variant(h.variant, scheme, bnd, ref), 2) / 2
-                                  : resident_waves(step2_fn_variant(h.variant, scheme, bnd, ref), wpb);
+    if (tb >= 3) {
+        const int waves = resident_waves(stepc_fn_variant(h.variant, scheme, tb, ref), tb), cus = device_cus();
+        const int rows = waves > 0 && cus > 0 ? chain_rows(h, scheme, tb, waves / tb, cus) : 0;
+        if (rows) return rows;
+    } else if (tb == 2) {
+        const int slots = pairs ? resident_waves(step2p_fn_variant(h.variant, scheme, bnd, ref), 2) / 2
+                                : resident_waves(step2_fn_variant(h.variant, scheme, bnd, ref), wpb);
         const int strip = SLOTS - 2 * tb, nstrips = (h.nx + strip - 1) / strip;
         int best = 0, least = 0;
         for (int k = 1; k <= 8; ++k) {
@@ -1090,12 +1129,7 @@ int march_rows(lbfv_ctx *c, int scheme, int tb) {
 }
 
 int device_cus(lbfv_ctx *c) {
-    int dev = 0;
-    if (!c->cus && (hipGetDevice(&dev) != hipSuccess ||
-                    hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)) {
-        (void)hipGetLastError();
-        c->cus = 0;
-    }
+    if (!c->cus) c->cus = device_cus();
     return c->cus;
 }
 // the shape of a march of tb steps per launch

@@ -134,3 +134,17 @@ def test_single_steps_move_the_state_back(kind, few):
             assert not moved(lambda: ctx.dugks_step(1)) and not moved(lambda: ctx.dugks_step(4))
             outs.append(ctx.get_f())
     assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
+
+
+@pytest.mark.parametrize("form,n,low,high", [("f64", 300, 8, 12), ("f64", 8, 1, 8), ("f32", 300, 3, 12),
+                                             ("f32", 4096, 32, 100), ("f16", 3000, 32, 100)])
+def test_default_heights_of_chains(form, n, low, high):
+    """Four steps per launch without a height: on a small mesh not so low that chains share a CU for
+    little, nor, on a large one in FP32 arithmetic, so high that a launch is one round of tall blocks."""
+    xf, yf = I.uniform_faces(n), I.uniform_faces(n)
+    compute, storage = FORMS[form]
+    with L.Context(xf, yf, 0.01, I.cfl_dt(xf, yf, 0.5), bcs=["periodic"] * 4, compute=compute, storage=storage) as ctx:
+        ctx.set_time_block(4)
+        rows = ctx.get_tile()[0]
+    print(form, n, rows)
+    assert low <= rows <= high
