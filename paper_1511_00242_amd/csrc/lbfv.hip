@@ -288,6 +288,7 @@ struct lbfv_batch {
                                                    // steps, two steps with pairs of waves; per scheme
     hipGraphExec_t gexec[4][2] = {};              // per scheme (+2: the patch form) and starting buffer
     int form = FORM_AUTO;
+    bool captured = false;           // a program may hold captured work on the buffers
     // the patch form, per scheme: halo and waves of all patches (halo 0: not planned yet; waves
     // 0: the batch takes none), their count and what the cost model gives them, us per step
     struct Patches {
@@ -1429,8 +1430,8 @@ int set_layout(lbfv_ctx *c, int w) {
     return LBFV_OK;
 }
 
-// How a call of n steps advances the context.  per: most steps of a launch.  exact: no shape was
-// asked for, so the call behaves as one-step launches do: checks fall due at their step, and the
+// How a call of n steps advances the context.  per: most steps of a launch.  exact: the call behaves
+// as one-step launches do, since no shape was asked for: checks fall due at their step, and the
 // state ends in the buffer that n launches would leave it in (a program may replay captured work
 // that names that buffer).
 struct Advance {
@@ -1469,7 +1470,10 @@ int plan_advance(lbfv_ctx *c, int scheme, int n, Advance &a) {
         // marches run in every layout)
         return c->pinned ? (int)LBFV_OK : set_layout(c, SLOTS - 2 * h.tblock);
     }
-    a.exact = true;
+    // The autotuner may pick launches of several steps in any form: their calls take the fewest
+    // launches, as those of marches do, unless a program holds captured work (calls of two steps of a
+    // tuned 256^2 FP64 BKG vortex: 14.1 us in two launches, 10.0 in one of a march).
+    a.exact = c->form == FORM_AUTO || c->pinned;
     // a stream under capture gets one-step launches
     if (capturing) return LBFV_OK;
     // 16-bit storage is rounded after every step unless several per launch were asked for
@@ -2462,7 +2466,10 @@ int batch_use_patches(lbfv_batch *b, int scheme, bool &yes) {
     if (b->form == FORM_MARCH) return LBFV_OK;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(b->stream, &capture) != hipSuccess) (void)hipGetLastError();
-    else if (capture != hipStreamCaptureStatusNone) return LBFV_OK;
+    else if (capture != hipStreamCaptureStatusNone) {
+        b->captured = true;
+        return LBFV_OK;
+    }
     if (b->form == FORM_AUTO)
         for (const auto &h : b->cases)
             if ((int64_t)h.nx * h.ny > BATCH_PATCH_CELLS) return LBFV_OK;
@@ -3024,11 +3031,13 @@ int lbfv_batch_step(lbfv_batch *b, int scheme, int32_t n) {
         b->parity ^= (int)(replay & 1);
         n -= (int32_t)(per * replay);
     }
-    // (patches: an even or odd number of launches as the steps are, like one-step launches)
+    // (patches: an even or odd number of launches as the steps are, like one-step launches, unless
+    // the autotuner picked them and no work was captured)
+    const bool exact = patch && (b->form == FORM_AUTO || b->captured);
     int64_t cells = 0;
     for (const auto &h : b->cases) cells += (int64_t)h.nx * h.ny;
     const bool single_marches = patch && cells > batch_single_cells(is_f64(b->variant));
-    Cut cut(n, per, patch, single_marches);
+    Cut cut(n, per, exact, single_marches);
     while (const int k = cut.next()) {
         st = patch && !(k == 1 && single_marches) ? batch_launch_patches(b, scheme, b->parity, k)
                                                   : batch_launch_one(b, scheme, b->parity, k == 2);
