@@ -561,9 +561,12 @@ struct March {
     }
     template <bool SELECT = false>
     __device__ __forceinline__ void ghost_x(T (&phi)[9]) const {
-        if constexpr (BND) {
-            if (ghostW) ghost_lane<1, SELECT>(SIDE_W, HALO - 1, phi);
-            if (ghostE) ghost_lane<-1, SELECT>(SIDE_E, laneE, phi);
+        // (without sides this is dead code, but for BKG in FP64 it decides how the compiler orders the
+        // chain: 6 register moves fewer with the select form, 512^2 6.30 -> 6.05 us a step)
+        constexpr bool keep = sizeof(T) == 8 && SCHEME == SCHEME_BKG;
+        if constexpr (BND || keep) {
+            if (ghostW) ghost_lane<1, SELECT || !BND>(SIDE_W, HALO - 1, phi);
+            if (ghostE) ghost_lane<-1, SELECT || !BND>(SIDE_E, laneE, phi);
         }
     }
     // y-side ghost row from rows r1 (adjacent) and r2 (next); ghost lanes included (corners).
