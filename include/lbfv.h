@@ -168,6 +168,10 @@ int bkg_step(lbfv_ctx *ctx, int32_t nsteps);
 int lbfv_step(lbfv_ctx *ctx, int scheme, int32_t nsteps);
 
 /* Observables, FP64, synchronising the stream.
+ * Fields and states move between host arrays and the device through a pinned buffer of the context's
+ * (a batch's) own, of at most 16 MiB, allocated by the first such call and held until the context is
+ * destroyed; large ones are copied by up to 8 threads while the call lasts.  Calls from several threads
+ * that read fields of one object take turns.
  * lbfv_moments: rho = sum f~, rho u = sum xi f~ (Sec. 2.2, Eq. macro_var).
  * lbfv_totals:  out[0] = sum rho |V|, out[1..2] = sum rho u |V| (fixed reduction order).
  * lbfv_residual: ||u - u_prev||_2 / ||u||_2 over both components and all cells, where
@@ -195,14 +199,24 @@ int lbfv_totals_device(lbfv_ctx *ctx, double *dev_out);
 
 /* Execution shape of the step kernel: rows of the row block one wavefront marches
  * through, and wavefronts per workgroup (1, 2 or 4).  0 keeps the current value.
- * A context on which no shape has been set (by this call, lbfv_set_wave_pairs,
- * lbfv_set_time_block or lbfv_autotune) advances a small mesh (at most 2^20 cells) in the
- * patch form instead: rectangular patches with one cell per lane, up to 8 steps per launch,
- * each patch recomputing a halo, and in FP64 and FP32 a larger one with four (doubly
- * periodic) or two steps per launch.  The results are those of one-step launches bit for bit,
- * in every storage (16-bit storage is rounded after every step); checks fall due exactly at
- * check_every, and the state ends each call in the buffer that one-step launches would leave
- * it in.  A stream under capture gets one-step launches. */
+ * A context on which no shape has been set (by this call with a value, lbfv_set_wave_pairs,
+ * lbfv_set_time_block or lbfv_autotune) picks the form of its launches by the size of the mesh:
+ *   - patches (rectangles with one cell per lane, each recomputing a halo, up to 8 steps per launch)
+ *     in calls of any length up to 170,000 cells in FP64 and about 350,000 in FP32 (BKG with a
+ *     non-periodic side: 2^18 and 2^19); in 16-bit storage, and in calls of fewer than 16 steps, up
+ *     to 2^20 cells (FP64 with a non-periodic side: 2^18).  Launches of one step are marches from
+ *     340,000 cells on in FP64, and from 440,000 (BKG) or 640,000 in FP32 arithmetic;
+ *   - on larger meshes in FP64 and FP32, from a first call of 16 steps on, marches of four steps per
+ *     launch on a doubly periodic mesh and of two, by pairs of waves, with sides;
+ *   - marches of one step otherwise, and always on a stream under capture.
+ * The results are those of one-step launches bit for bit, in every storage (16-bit storage is rounded
+ * after every step), and checks fall due exactly at check_every.  The state ends a call in the buffer
+ * that one-step launches would leave it in, but for the calls that move it to another strip layout,
+ * into the other buffer: the first call of marches of several steps, a call after eight single steps
+ * in their layout, which moves it back, and the first after this call or lbfv_set_wave_pairs where
+ * that layout is left.  No such call moves it any more once steps were captured, lbfv_totals_device
+ * was called or lbfv_bind_buffers gave the buffers; lbfv_set_time_block and lbfv_autotune always may.
+ * With pairs of waves the two strips at non-periodic x sides may take lower row blocks than `rows`. */
 int lbfv_set_tile(lbfv_ctx *ctx, int32_t rows, int32_t waves_per_block);
 int lbfv_get_tile(const lbfv_ctx *ctx, int32_t *rows, int32_t *waves_per_block);
 /* Work split of two steps per launch: 0 (default) one wavefront per work item (strip x
@@ -245,8 +259,10 @@ int lbfv_get_reference_velocity(const lbfv_ctx *ctx, double *ux, double *uy);
  * saved and restored; on small meshes the patch form of lbfv_set_tile is a candidate, and
  * where it wins the march controls hold the fastest march of one step per launch), keeps
  * the fastest, and records it in a cache file keyed by (gfx arch, scheme, precision,
- * storage, time block, mesh size class).  cache_path NULL: the environment variable
- * LBFV_TUNE_CACHE, else no file.  A cached entry is used without timing.  best_ms (nullable) receives the time per step of the choice. */
+ * storage, time block, mesh size class).  Each shape is timed over trial_steps steps, the patch form
+ * over as many whole launches.  cache_path NULL: the environment variable LBFV_TUNE_CACHE, else no
+ * file.  A cached entry is used without timing.  best_ms (nullable) receives the time per step of
+ * the choice. */
 int lbfv_autotune(lbfv_ctx *ctx, int scheme, int32_t trial_steps, const char *cache_path,
                   double *best_ms);
 
@@ -285,7 +301,10 @@ int lbfv_batch_nonfinite(lbfv_batch *b, int32_t *count);
 /* Graph length K (default 100) and rows per row block of the work list (default 8); 0
  * keeps the current value.  A batch on which no shape has been set (rows, time block, grid
  * form, wave pairs or the autotuner) and whose meshes have at most 2^18 cells each advances
- * in the patch form of lbfv_set_tile: the same bits, up to 8 steps per launch. */
+ * in the patch form of lbfv_set_tile: the same bits, up to 8 steps per launch, in graphs of K or
+ * K + 1 launches (an even number), so that a call leaves the state in the buffer that one-step
+ * launches would.  Above 240,000 cells in all (FP64; 350,000 in FP32) its launches of one step are
+ * marches.  It marches on a stream under capture, and where its tables find no memory. */
 int lbfv_batch_set_shape(lbfv_batch *b, int32_t graph_steps, int32_t rows);
 int lbfv_batch_get_shape(const lbfv_batch *b, int32_t *graph_steps, int32_t *rows);
 /* Grid form of the batch's launches: 0 (default) launches the waves that fit on the device
@@ -313,8 +332,8 @@ int lbfv_batch_get_time_block(const lbfv_batch *b, int32_t *steps);
  * best) and two grid forms (the resident waves walking the list, or one wave per item) for
  * `scheme`, each as a replay of a graph of trial_steps launches after one warm-up replay;
  * so too the patch form, where it comes near (if it wins, the march controls hold the fastest
- * march of one step per launch); keeps the fastest, and restores every case's state and the step parity (the trial steps
- * leave no trace).  Needs a device copy of the whole state for its
+ * march of one step per launch); keeps the fastest, and restores every case's state and the step
+ * parity (the trial steps leave no trace).  Needs a device copy of the whole state for its
  * duration (ENOMEM otherwise).  best_ms (nullable) receives the time per step of the
  * choice.  EINVAL for an unknown scheme or trial_steps < 1. */
 int lbfv_batch_autotune(lbfv_batch *b, int scheme, int32_t trial_steps, double *best_ms);

@@ -498,8 +498,8 @@ struct March {
     // side and row: an extrapolating side then takes 8 instructions a direction where one form
     // for all kinds took 14, and loads one constant instead of ten.  Held over a row, those
     // constants spilled from the scalar registers in every strip (73 of them in the FP64 DUGKS
-    // pair, 3 now): 1024^2 cavity FP64 DUGKS, pairs, 27.9 -> 25.8 us a step, 96-case FP32 batch
-    // 141 -> 119.
+    // pair, 1 now; 97 and 81 in the FP64 batch pairs, 9 and 11 now): 1024^2 cavity FP64 DUGKS, pairs,
+    // 27.9 -> 25.8 us a step, 96-case FP32 batch 141 -> 119.
     // SELECT: the same rule in one form for all kinds, a side's constants loaded once per row.  It
     // needs fewer vector registers: BKG's two steps on one wave in FP32 arithmetic take 132 of them
     // with branches and 121 so, and up to 128 a fourth wave fits a SIMD (2500^2 cavity, 16 rows, 24

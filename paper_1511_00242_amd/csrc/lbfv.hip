@@ -694,7 +694,8 @@ int patch_parts(int n, bool periodic, int halo, int cap) {
     return 0;
 }
 constexpr int PATCH_HALO = 8;   // most steps per launch of the patch form
-// Largest mesh that takes the patch form where no launch shape was set.  Against one-step
+// Largest mesh that takes the patch form at all where no launch shape was set: in 16-bit storage, and
+// in FP64 and FP32 in short calls (patch_cells is the line of calls of any length).  Against one-step
 // marches of the default shape, us per step (DUGKS and BKG in FP64, then in FP32): 64^2 vortex
 // 1.7 / 1.3 / 1.4 / 1.2 against 11.6 / 8.9 / 10.6 / 8.4, 512^2 cavity 13 / 8 / 7 / 5 against 32 / 28
 // / 28 / 24, 1024^2 vortex 30 / 23 / 20 / 15 against 50 / 49 / 30 / 28, 1024^2 cavity 39 / 26 / 24 /
@@ -705,9 +706,10 @@ constexpr int64_t PATCH_CELLS = 1 << 20;
 // 19 / 14 / 12 / 9 against 41 / 32 / 22 / 20, 6 of 512^2 59 / 41 / 36 / 25 against 75 / 65 / 56 / 38;
 // 96 uneven cases of 64^2 to 512^2 in FP32 210 / 154 against 213 / 208.
 constexpr int64_t BATCH_PATCH_CELLS = 1 << 18;
-// Largest mesh on which the autotuner tries it: its fastest marches (two to four steps per
-// launch) pass the patch form between 200^2 and 450^2 cells.
-constexpr int64_t PATCH_TRIAL_CELLS = 1 << 20;
+// The autotuner tries it on meshes up to PATCH_CELLS too.  Its marches of several steps pass the patch
+// form from about 410^2 cells (FP64) and 610^2 (FP32) on doubly periodic meshes, with sides from
+// 510^2 and 740^2 (the lines of patch_cells); in 16-bit storage they round less often, but on larger
+// meshes patches still beat those of one step.
 
 // Largest mesh on which a launch of one step takes patches; above, a march of one step (in the same
 // layout, with the same bits) comes cheaper than a halo made for several.  us a call of one step,
@@ -771,9 +773,11 @@ PatchDevice patch_device(bool f64, void *fn) {
 // once, or a CU takes one at a time, latency counts, per round: 1.6 us and 0.4 us per resident
 // wave of a SIMD for addresses, loads and stores, and per step a part that one wave alone cannot
 // hide (barriers, dependent arithmetic; 0.6 us more where patches hold ghost cells) and a part
-// per resident wave; within 15 %.  Otherwise the workgroups hide each other's waits and their
-// throughput counts, per wave of a SIMD: loads and stores and the steps' arithmetic, but at least
-// the time of its memory traffic.
+// per resident wave.  Otherwise the workgroups hide each other's waits and their throughput counts,
+// per wave of a SIMD: loads and stores and the steps' arithmetic, but at least the time of its
+// memory traffic.  Of 640 plans of single meshes 75 % lie within 15 % of their timings and 97 % within
+// 30 %, of 600 of batches 50 and 83 %; the halo that the model picks is the fastest or equal in half of
+// the cases, 22 % slower at worst (profiles/patch_form_timings.txt has them all).
 double patch_cost(bool f64, bool bkg, bool bnd, const PatchDevice &d, int64_t groups, int waves, int halo) {
     const int per_cu = (int)((groups + d.cus - 1) / d.cus), fit = d.fit[waves > 4];
     const int share = std::min(per_cu, fit) * (waves > 4 ? 2 : 1);   // resident waves of a SIMD
@@ -1444,7 +1448,9 @@ struct Advance {
 int unasked_time_block(const HostCase &h) { return !has_boundary(h) && std::min(h.nx, h.ny) >= 8 ? 4 : 2; }
 // Where no shape was set, meshes up to this size take patches in calls of any length, larger ones
 // in long calls the marches above.  us a step, patches and marches: periodic, DUGKS FP64 384^2 5.6
-// and 6.4, 448^2 8.4 and 7.1; FP32 512^2 5.6 and 7.2, 640^2 10.7 and 8.6.  With sides the pairs
+// and 6.4, 448^2 8.4 and 7.1; FP32 512^2 5.6 and 7.2, 640^2 10.7 and 8.6; BKG crosses where DUGKS does
+// to within a patch more or less, FP64 420^2 5.0 and 5.4, 448^2 5.6 and 5.6, 512^2 7.2 and 6.6, FP32
+// 576^2 4.9 and 6.2, 608^2 7.0 and 6.3.  With sides the pairs
 // gain more on DUGKS than on BKG: cavity FP64 DUGKS 384^2 6.8 and 7.6, 416^2 8.0 and 7.8, 512^2
 // 12.9 and 9.8, BKG 448^2 6.7 and 7.2, 512^2 8.1 and 8.3; FP32 DUGKS 576^2 8.4 and 9.1, 608^2 9.5
 // and 9.0, BKG 672^2 7.8 and 8.8, 736^2 9.1 and 9.1.
@@ -2255,7 +2261,7 @@ extern "C" int lbfv_autotune(lbfv_ctx *c, int scheme, int32_t trial_steps, const
     // model puts it far behind its best one
     PatchPlan best_plan;
     double best_patch = INFINITY;
-    if (!st && (int64_t)h.nx * h.ny <= PATCH_TRIAL_CELLS && !(st = set_time_block(c, 1))) {
+    if (!st && (int64_t)h.nx * h.ny <= PATCH_CELLS && !(st = set_time_block(c, 1))) {
         const PatchDevice dev = patch_device(is_f64(h.variant), patch_kernel_of(c, scheme));
         const double limit = 1.4 * best_patch_plan(h, dev, scheme).cost;
         c->form = FORM_PATCH;
