@@ -1553,6 +1553,7 @@ int do_steps(lbfv_ctx *c, int scheme, int32_t n) {
         // mesh continues with two steps per launch
         if ((st = set_time_block(c, 2))) return st;
     }
+    if (n == 0) return LBFV_OK;   // (nor does it move the state to another layout)
     current_ext(h, ext);
     Advance adv;
     if ((st = plan_advance(c, scheme, n, adv))) return st;

@@ -137,3 +137,14 @@ def test_the_time_block_that_is_set_is_the_one_that_runs():
     print(unasked, asked, flush=True)
     assert steps(unasked) and all("step2bp" in n for n in steps(unasked))
     assert steps(asked) and not any("step2bp" in n for n in steps(asked))
+
+
+def test_a_call_of_no_steps_moves_nothing():
+    w = I.taylor_green(450)
+    with L.Context(w.xf, w.yf, w.tau, w.dt, bcs=w.bcs, check_every=0) as ctx:
+        ctx.init_equilibrium(w.rho, w.ux, w.uy)
+        ctx.dugks_step(32)
+        ctx.set_tile(8, 4)
+        moved = lambda n: any("relayout" in k for k in kernels_of(lambda: ctx.dugks_step(n)))   # noqa: E731
+        assert not moved(0)
+        assert moved(1) and not moved(1)
